@@ -56,7 +56,7 @@ typedef enum {
 
 /* Arithmetic of the X-engine (precision forms beyond the paper's FP32,
  * Sec. 2.5.1 and 2.5.2 use single precision throughout):
- *   FP32: spectra kept in FP32, X-engine on the vector ALUs in FP32, partial
+ *   FP32: spectra kept in FP32, X-engine on the FP32 matrix cores, partial
  *         sums flushed to FP64 integrators every 2048 spectra.
  *   FP16: spectra scaled by 2^-e, e = ceil(log2(L)/2), rounded to binary16
  *         (ties to even); X-engine on FP16 matrix cores with FP32 accumulation,
@@ -223,10 +223,9 @@ mwax_status mwax_correlate(mwax_plan p);
 
 /* Emit up to max_ints completed integrations, oldest first, into d_vis
  * (complex64 in the given mwax_order; CHAN_TRI needs max_ints * L * P values,
- * TILE_BL max_ints * n_baselines * L * 4) and free their device slots (the
- * integrators are cleared, except in plans of a batch or stream whose next
- * X-engine work overwrites a slot anyway).  *n_emitted receives the count (0
- * if none is complete).  Integrations still in progress are kept. */
+ * TILE_BL max_ints * n_baselines * L * 4) and free their device slots.
+ * *n_emitted receives the count (0 if none is complete).  Integrations still in
+ * progress are kept. */
 mwax_status mwax_integrate(mwax_plan p, void *d_vis, int32_t max_ints, int32_t *n_emitted,
                            int32_t order);
 
@@ -350,7 +349,7 @@ mwax_status mwax_kernel_time(mwax_plan p, int32_t family, double *total_ms, int6
 typedef struct mwax_batch_s *mwax_batch;
 
 /* Create a batch of n (1..64) instances from cfgs[n].  All instances must use
- * the same xprec, INT8 or FP16 (FP32 runs on the vector ALUs and is not
+ * the same xprec, INT8 or FP16 (FP32 is not
  * batched: MWAX_E_UNSUPPORTED).  hip_stream: the stream every batch call
  * enqueues on; NULL makes the batch create its own stream, which like the
  * default stream's other users synchronises with the legacy default stream.

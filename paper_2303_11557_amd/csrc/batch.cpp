@@ -704,7 +704,7 @@ mwax_status mwax_batch_create(const mwax_config *cfgs, int32_t n, void *hip_stre
                         "6,400-point transform as a plan", i, d.fft_len);
     }
     if (cfgs[0].xprec == MWAX_X_FP32)
-        return fail(MWAX_E_UNSUPPORTED, "FP32 plans run on the vector ALUs and are not batched (use INT8 or FP16)");
+        return fail(MWAX_E_UNSUPPORTED, "FP32 plans are not batched (use INT8 or FP16)");
 
     mwax_batch b = new (std::nothrow) mwax_batch_s;
     if (!b) return fail(MWAX_E_NOMEM, "host allocation failed");

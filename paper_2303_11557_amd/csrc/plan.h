@@ -70,11 +70,12 @@ struct mwax_plan_s {
     int32_t dl_fps = 0;
     int64_t dl_pos0 = 0;
     double dl_nu = 0.0;             // sky frequency / coarse bandwidth
-    // Clear a slot's integrators when its integration is emitted.  Off only where
-    // every integration's first X-engine flush overwrites the whole slot
-    // (whole-segment INT8/FP16 work of a batch); mwax_correlate clears a slot
-    // itself before accumulating into one that was not cleared.
-    bool clear_on_emit = true;
+    // Clear a slot's integrators when its integration is emitted: on for batch
+    // instances whose X-engine work is chunked (their atomic adds need cleared
+    // slots).  Elsewhere the first flush of every integration overwrites the whole
+    // slot, and mwax_correlate clears a slot itself before a chunked launch adds
+    // into it.
+    bool clear_on_emit = false;
     // X-engine launches run whole segments (no K-chunks with atomic flushes).
     // Chunks fill the resident slots of a launch running alone; the stream
     // runtime sets this, because its two lanes fill each other's launch tails.

@@ -363,10 +363,6 @@ mwax_status create_plan(const mwax_config *cfg, void *hip_stream, mwax_plan *out
     p->slot_bytes = (size_t)integ_slot_bytes(p->xprec, p->T, p->L, p->P);
     p->slot_owner.assign(p->nslots, -1);
     p->slot_count.assign(p->nslots, 0);
-    // 6,400 channels: an integration's first X-engine flush overwrites its slot,
-    // so slots are not cleared when emitted (mwax_correlate clears one itself
-    // before a launch that would add into it)
-    if (p->L == kUltraFineL) p->clear_on_emit = false;
 
     // workspace buffers, in order
     const size_t esize = p->xprec == MWAX_X_INT8 ? 1 : (p->xprec == MWAX_X_FP16 ? 2 : 4);

@@ -19,9 +19,8 @@
 //   INT8: v_mfma_i32_32x32x32_i8, int32 partials flushed to int64 integrators
 //         at most every 65536 spectra (|partial| < 518160 * 4096 < 2^31).
 //   FP16: v_mfma_f32_32x32x16_f16, FP32 partials flushed to FP64 integrators.
-//   FP32: vector ALUs, 4 x 8 complex outputs per thread, two-level FP32
-//         partials (see xengine_f32) flushed to FP64 integrators every 2048
-//         spectra.
+//   FP32: v_mfma_f32_32x32x2_f32, two-level FP32 partials (see xengine_f32)
+//         flushed to FP64 integrators every 2048 spectra.
 #include <type_traits>
 
 #include "mwax_internal.h"
@@ -38,7 +37,6 @@ constexpr int kTile = kXTile;       // tile edge in inputs (single-plan launches
                                     // instance may take kTileSmall, see xengine_batch)
 constexpr int kTileSmall = kXTileSmall;
 constexpr int kThreads = 256;       // 4 waves
-constexpr int kKG = 4;              // row groups per LDS stage
 
 // Lower-triangle tile index t -> (I, J), I >= J, t = I(I+1)/2 + J.
 __device__ __forceinline__ void tile_ij(int t, int &I, int &J) {
@@ -725,123 +723,252 @@ __global__ void zero_i32_kernel(int32_t *p, int n) {
 }
 
 // ---------------------------------------------------------------------------
-// FP32 X-engine on the vector ALUs.  512 threads, 4 x 8 complex outputs each.
+// FP32 X-engine on the FP32 matrix cores (v_mfma_f32_32x32x2_f32).  One
+// instruction takes one spectrum: K = (re, im), lanes 0..31 carrying the real
+// and lanes 32..63 the imaginary parts, so
+//   Re V: A = (re1, im1), B = (re2, im2);  Im V: the same A, B2 = (-im2, re2).
+// A planar FP32 row half (4 spectra of one component) is one lane's operand of
+// four instructions; B2 is the other half of B's row, read from there.
 //
 // Two-level FP32 accumulation: each 16-spectrum stage is summed into an inner
 // accumulator, which is then added to an outer one; the outer one is flushed
-// to the FP64 integrator every 2048 spectra.  A single FP32 running sum is
-// biased: in the channels whose bin is a multiple of L/4 the spectra of
-// integer voltages are exact integers, their squares are 0 or 1 mod 4, and
-// once the running sum passes 2^24 every addition rounds the same way.  The
-// inner sums stay far below 2^24 (exact for those channels) and have evenly
-// spread low bits, so the outer additions round without a bias.
+// to FP64 every 2048 spectra.  A single FP32 running sum is biased: in the
+// channels whose bin is a multiple of L/4 the spectra of integer voltages are
+// exact integers, their squares are 0 or 1 mod 4, and once the running sum
+// passes 2^24 every addition rounds the same way.  The inner sums stay far
+// below 2^24 (exact for those channels) and have evenly spread low bits, so the
+// outer additions round without a bias.
 // ---------------------------------------------------------------------------
-constexpr int kF32Threads = 512;
-constexpr int kF32FlushGroups = 512;   // 2048 spectra per FP32 outer partial
+constexpr int kFT = kTileSmall;               // tile edge: 2 x 2 waves of one 32 x 32 block
+constexpr int kFG = 4;                        // row groups per stage: 16 spectra, one inner sum
+constexpr int kFGroup = kFT / 32 * kBlock;    // LDS bytes of one panel's row group
+constexpr int kFPanel = kFG * kFGroup;
+constexpr int kFStage = 2 * kFPanel;
+constexpr int kFFlush = 2048 / (4 * kFG);     // inner sums per FP32 outer sum
 
-__global__ __launch_bounds__(kF32Threads) void xengine_f32(XArgs a) {
-    constexpr int S = kKG * 4;   // spectra per stage
-    __shared__ __align__(16) float sAr[S][kTile], sAi[S][kTile], sBr[S][kTile], sBi[S][kTile];
+// One 32 x 32 block over one row group (4 spectra): a, b the lane's halves of
+// its A and B rows, b2 the other half of its B row; sign: 0x80000000 for the
+// lanes of the real parts (their B2 operand is -im), else 0.
+__device__ __forceinline__ void mma_f32_group(float4 a, float4 b, float4 b2, uint32_t sign, v16f &re, v16f &im) {
+    const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w}, cv[4] = {b2.x, b2.y, b2.z, b2.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        re = __builtin_amdgcn_mfma_f32_32x32x2f32(av[e], bv[e], re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f32_32x32x2f32(av[e], __uint_as_float(__float_as_uint(cv[e]) ^ sign), im, 0, 0, 0);
+    }
+}
 
+// One workgroup = one channel x one 64 x 64 tile: the stages of both panels are
+// copied straight into LDS, one ahead of the matrix work, into two buffers
+// (separate LDS objects, so that a read of one does not wait for the copies
+// landing in the other).  A stage is 32 instructions of 64 cycles per wave, long
+// enough to cover the copies with one barrier per stage; 32 KB of LDS and at most
+// 128 registers put four workgroups on a CU.  Bound by the matrix cores (75 % of
+// their cycles busy; the rest is the last, partly filled round of workgroups and
+// the flushes): 256 inputs, 128 channels, 5,000 spectra take 1.7-1.8 ms, 96
+// TFLOP/s of the 151 a large library product reaches, where 4 x 8 outputs per
+// thread on the vector ALUs took 4.6 ms.
+__global__ __launch_bounds__(kThreads, 4) void xengine_f32(XArgs a) {
+    __shared__ __align__(16) uint8_t buf0[kFStage], buf1[kFStage];
     const int nb = gridDim.x;
     const int lin = xcd_logical(blockIdx.x, nb);
     const int c = lin / a.ntiles;
     int I, J;
     tile_ij(lin - c * a.ntiles, I, J);
-    const int rowA0 = I * kTile, rowB0 = J * kTile;
-    const int tid = threadIdx.x;
-    const int ty = tid >> 4, tx = tid & 15;        // rows ty*4 + i, cols tx*8 + j
-    const bool active = !(I == J && tx * 8 > ty * 4 + 3) && (rowA0 + ty * 4 < a.n_in) &&
-                        (rowB0 + tx * 8 < a.n_in);
+    const int rowA0 = I * kFT, rowB0 = J * kFT;
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    // the wave of each block turns with the tile: a diagonal tile's idle wave (and
+    // its SIMD) is another one from workgroup to workgroup
+    const int role = (wave + lin) & 3, wr = role >> 1, wc = role & 1;
+    const bool active = !((I == J && wr < wc) || rowA0 + wr * 32 >= a.n_in || rowB0 + wc * 32 >= a.n_in);
 
-    float inr[4][8], ini[4][8], outr[4][8], outi[4][8];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) inr[i][j] = ini[i][j] = outr[i][j] = outi[i][j] = 0.0f;
-
-    const uint8_t *base = a.chan + ((int64_t)c * a.NG + a.grp0) * (int64_t)a.n_in * kRowBytes;
+    // copies: waves 0, 1 move 32 rows each of the A panel, waves 2, 3 of the B
+    // panel.  Rows past the last input are read from a clamped address: they reach
+    // only outputs that are never flushed.
+    const int cblk = wave & 1, crow = cblk * 32 + l32;
+    const uint32_t offR = (uint32_t)min((wave < 2 ? rowA0 : rowB0) + crow, a.n_in - 1) * kRowBytes + half * 16;
+    const uint32_t offZ = (uint32_t)crow * kRowBytes + half * 16;
     const int64_t gstride = (int64_t)a.n_in * kRowBytes;
-
-    auto flush = [&]() {
-        if (!active) return;
+    const uint8_t *base = a.chan + ((int64_t)c * a.NG + a.grp0) * gstride;
+    const int ldst = (wave >> 1) * kFPanel + cblk * kBlock;
+    const int nstages = (a.ngrp + kFG - 1) / kFG;
+    auto copy_stage = [&](int s, uint8_t *buf) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int n1 = rowA0 + ty * 4 + i;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int n2 = rowB0 + tx * 8 + j;
-                if (n1 < a.n_in && n2 <= n1) {
-                    double2 *dst = reinterpret_cast<double2 *>(a.integ) + (int64_t)c * a.P +
-                                   (int64_t)n1 * (n1 + 1) / 2 + n2;
-                    double2 v = *dst;
-                    v.x += (double)outr[i][j];
-                    v.y += (double)outi[i][j];
-                    *dst = v;
-                }
-                outr[i][j] = outi[i][j] = 0.0f;
-            }
+        for (int k = 0; k < kFG; ++k) {
+            const int g = s * kFG + k;
+            const uint8_t *src = g < a.ngrp ? base + g * gstride + offR : kZeroGroup + offZ;
+            __builtin_amdgcn_global_load_lds(src, buf + k * kFGroup + ldst, 16, 0, 0);
         }
     };
 
-    int since_flush = 0;
-    for (int g0 = 0; g0 < a.ngrp; g0 += kKG) {
-        __syncthreads();
-        // stage kKG groups of both panels: 16-byte units, transposed to [spectrum][row]
-        for (int u = tid; u < kKG * kTile * 2; u += kF32Threads) {
-            const int k = u / (kTile * 2);
-            const int row = (u >> 1) & (kTile - 1), h = u & 1;
-            const bool gok = g0 + k < a.ngrp;
-            float4 va = make_float4(0.f, 0.f, 0.f, 0.f), vb = va;
-            if (gok && rowA0 + row < a.n_in)
-                va = *reinterpret_cast<const float4 *>(base + (g0 + k) * gstride + (int64_t)(rowA0 + row) * kRowBytes + h * 16);
-            if (gok && rowB0 + row < a.n_in)
-                vb = *reinterpret_cast<const float4 *>(base + (g0 + k) * gstride + (int64_t)(rowB0 + row) * kRowBytes + h * 16);
-            float (*da)[kTile] = h ? sAi : sAr;
-            float (*db)[kTile] = h ? sBi : sBr;
-            da[k * 4 + 0][row] = va.x; da[k * 4 + 1][row] = va.y; da[k * 4 + 2][row] = va.z; da[k * 4 + 3][row] = va.w;
-            db[k * 4 + 0][row] = vb.x; db[k * 4 + 1][row] = vb.y; db[k * 4 + 2][row] = vb.z; db[k * 4 + 3][row] = vb.w;
-        }
-        __syncthreads();
-        if (active) {
-#pragma unroll 2
-            for (int s = 0; s < S; ++s) {
-                const float4 a0 = *reinterpret_cast<const float4 *>(&sAr[s][ty * 4]);
-                const float4 a1 = *reinterpret_cast<const float4 *>(&sAi[s][ty * 4]);
-                const float4 b0 = *reinterpret_cast<const float4 *>(&sBr[s][tx * 8]);
-                const float4 b1 = *reinterpret_cast<const float4 *>(&sBr[s][tx * 8 + 4]);
-                const float4 b2 = *reinterpret_cast<const float4 *>(&sBi[s][tx * 8]);
-                const float4 b3 = *reinterpret_cast<const float4 *>(&sBi[s][tx * 8 + 4]);
-                const float ar[4] = {a0.x, a0.y, a0.z, a0.w};
-                const float ai[4] = {a1.x, a1.y, a1.z, a1.w};
-                const float br[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-                const float bi[8] = {b2.x, b2.y, b2.z, b2.w, b3.x, b3.y, b3.z, b3.w};
+    const int fa_off = wr * kBlock + half * 512 + l32 * 16;
+    const int fb_off = kFPanel + wc * kBlock + half * 512 + l32 * 16;
+    const int fb2_off = fb_off + (half ? -512 : 512);
+    const uint32_t sign = half ? 0u : 0x80000000u;
+    v16f outr{}, outi{};
+    auto compute = [&](const uint8_t *st) {
+        v16f re{}, im{};
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+        for (int k = 0; k < kFG; ++k)
+            mma_f32_group(*reinterpret_cast<const float4 *>(st + k * kFGroup + fa_off),
+                          *reinterpret_cast<const float4 *>(st + k * kFGroup + fb_off),
+                          *reinterpret_cast<const float4 *>(st + k * kFGroup + fb2_off), sign, re, im);
+        outr += re;
+        outi += im;
+    };
+    // the outer sums into the FP64 integrators; the first flush of a segment that
+    // starts its integration stores instead of adding
+    bool store = a.first != 0;
+    auto flush = [&]() {
+        // opaque, so that the 16 addresses are not formed ahead of the K loop and
+        // held in registers through it
+        int fr0 = rowA0 + wr * 32, fc0 = rowB0 + wc * 32;
+        asm volatile("" : "+s"(fr0), "+s"(fc0));
+        double2 *dst0 = reinterpret_cast<double2 *>(a.integ) + (int64_t)c * a.P;
+        const int n2 = fc0 + l32;
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        inr[i][j] = fmaf(ar[i], br[j], inr[i][j]);
-                        inr[i][j] = fmaf(ai[i], bi[j], inr[i][j]);
-                        ini[i][j] = fmaf(ai[i], br[j], ini[i][j]);
-                        ini[i][j] = fmaf(-ar[i], bi[j], ini[i][j]);
-                    }
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    outr[i][j] += inr[i][j];
-                    outi[i][j] += ini[i][j];
-                    inr[i][j] = ini[i][j] = 0.0f;
+        for (int r = 0; r < 16; ++r) {
+            const int n1 = fr0 + (r >> 2) * 8 + half * 4 + (r & 3);
+            if (n1 < a.n_in && n2 <= n1) {
+                double2 *dst = dst0 + (int64_t)n1 * (n1 + 1) / 2 + n2;
+                double2 v = make_double2((double)outr[r], (double)outi[r]);
+                if (!store) {
+                    const double2 old = *dst;
+                    v.x += old.x;
+                    v.y += old.y;
                 }
+                *dst = v;
+            }
         }
-        since_flush += kKG;
-        if (since_flush >= kF32FlushGroups) {
-            flush();
-            since_flush = 0;
+        outr = v16f{};
+        outi = v16f{};
+        store = false;
+    };
+
+    copy_stage(0, buf0);
+    __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
+    asm volatile("s_barrier" ::: "memory");
+    auto iteration = [&](int s, uint8_t *cur, uint8_t *next) {
+        copy_stage(s + 1, next);           // last read one iteration ago, behind a barrier
+        if (active && s < nstages) compute(cur);
+        __builtin_amdgcn_s_waitcnt(0x0070);
+        asm volatile("s_barrier" ::: "memory");
+    };
+    static_assert(kFFlush % 2 == 0, "flushes fall between pairs of stages");
+    for (int s0 = 0; s0 < nstages; s0 += kFFlush) {
+        const int s1 = min(nstages, s0 + kFFlush);
+        for (int s = s0; s < s1; s += 2) {
+            iteration(s, buf0, buf1);
+            iteration(s + 1, buf1, buf0);
+        }
+        if (active) flush();
+    }
+}
+
+// Small launches (few tiles or channels, where 64 x 64 tiles would leave CUs
+// idle behind one long serial K loop each): one workgroup = one channel x one
+// 32 x 32 block, its eight waves taking the 16-spectrum stages in turn, straight
+// from global memory (a row group of a block is 1 KB contiguous).  Each wave
+// keeps FP64 totals of its flushed outer sums; they are added over the waves in a
+// fixed order, so the result does not depend on timing.  32 inputs, 128 channels,
+// 1,000 spectra: a 535 us step became 38 us (one 128-edge workgroup per channel
+// ran its 63 stages one after another on half of the CUs).
+constexpr int kFSWaves = 8;
+__global__ __launch_bounds__(64 * kFSWaves, 2) void xengine_f32_small(XArgs a) {
+    __shared__ double2 part[kFSWaves / 2][16][64];
+    const int nb = gridDim.x;
+    const int lin = xcd_logical(blockIdx.x, nb);
+    const int c = lin / a.ntiles;
+    int I, J;
+    tile_ij(lin - c * a.ntiles, I, J);
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int64_t gstride = (int64_t)a.n_in * kRowBytes;
+    const uint8_t *base = a.chan + ((int64_t)c * a.NG + a.grp0) * gstride;
+    const uint8_t *pa = base + min(I * 32 + l32, a.n_in - 1) * kRowBytes + half * 16;
+    const uint8_t *pb = base + min(J * 32 + l32, a.n_in - 1) * kRowBytes;
+    const uint32_t sign = half ? 0u : 0x80000000u;
+    const int nstages = (a.ngrp + kFG - 1) / kFG;
+
+    float4 fa[kFG], fb[kFG], fb2[kFG];
+    auto fetch = [&](int s) {
+#pragma unroll
+        for (int k = 0; k < kFG; ++k) {
+            const int g = s * kFG + k;
+            const int64_t o = (int64_t)min(g, a.ngrp - 1) * gstride;
+            fa[k] = *reinterpret_cast<const float4 *>(pa + o);
+            fb[k] = *reinterpret_cast<const float4 *>(pb + o + half * 16);
+            fb2[k] = *reinterpret_cast<const float4 *>(pb + o + (16 - half * 16));
+            if (g >= a.ngrp) fa[k] = make_float4(0.f, 0.f, 0.f, 0.f), fb[k] = fa[k], fb2[k] = fa[k];
+        }
+    };
+    v16f outr{}, outi{};
+    double2 tot[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) tot[r] = make_double2(0.0, 0.0);
+    auto collect = [&]() {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            tot[r].x += (double)outr[r];
+            tot[r].y += (double)outi[r];
+        }
+        outr = v16f{};
+        outi = v16f{};
+    };
+    int inner = 0;
+    if (wave < nstages) fetch(wave);
+    for (int s = wave; s < nstages; s += kFSWaves) {
+        float4 xa[kFG], xb[kFG], xb2[kFG];
+#pragma unroll
+        for (int k = 0; k < kFG; ++k) xa[k] = fa[k], xb[k] = fb[k], xb2[k] = fb2[k];
+        if (s + kFSWaves < nstages) fetch(s + kFSWaves);
+        v16f re{}, im{};
+#pragma unroll
+        for (int k = 0; k < kFG; ++k) mma_f32_group(xa[k], xb[k], xb2[k], sign, re, im);
+        outr += re;
+        outi += im;
+        if (++inner == kFFlush) {
+            collect();
+            inner = 0;
         }
     }
-    if (since_flush > 0) flush();
+    collect();
+    // waves 4 .. 7 hand their totals to waves 0 .. 3, then 2, 3 to 0, 1, then 1 to 0
+#pragma unroll
+    for (int h = kFSWaves / 2; h > 0; h >>= 1) {
+        if (wave >= h && wave < 2 * h) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) part[wave - h][r][lane] = tot[r];
+        }
+        __syncthreads();
+        if (wave < h) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const double2 v = part[wave][r][lane];
+                tot[r].x += v.x;
+                tot[r].y += v.y;
+            }
+        }
+        __syncthreads();
+    }
+    if (wave != 0) return;
+    double2 *dst0 = reinterpret_cast<double2 *>(a.integ) + (int64_t)c * a.P;
+    const int n2 = J * 32 + l32;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int n1 = I * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+        if (n1 < a.n_in && n2 <= n1) {
+            double2 *dst = dst0 + (int64_t)n1 * (n1 + 1) / 2 + n2;
+            double2 v = tot[r];
+            if (!a.first) {
+                const double2 old = *dst;
+                v.x += old.x;
+                v.y += old.y;
+            }
+            *dst = v;
+        }
+    }
 }
 
 }  // namespace
@@ -853,14 +980,22 @@ int xengine_tile_count(int n_in, int te) {
 }
 
 namespace {
+// Compute units of the device (read once; every device of a node is the same).
+int device_cus() {
+    static const int cus = [] {
+        int dev = 0, n = 0;
+        (void)hipGetDevice(&dev);
+        return hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0 ? n : 256;
+    }();
+    return cus;
+}
+
 // Resident workgroups of the single-plan MFMA kernel on the current device.
 int resident_slots() {
     static int slots = 0;
     if (slots == 0) {
-        int dev = 0, cus = 0, per_cu = 0;
-        (void)hipGetDevice(&dev);
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-            cus = 256;
+        int per_cu = 0;
+        const int cus = device_cus();
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
                 &per_cu, reinterpret_cast<const void *>(&xengine_mfma<MWAX_X_INT8>), kThreads, 0) != hipSuccess ||
             per_cu < 1)
@@ -900,7 +1035,6 @@ void set_chunks(int xprec, XArgs &a) {
 }  // namespace
 
 bool xengine_accumulates(int xprec, const XArgs &args) {
-    if (xprec == MWAX_X_FP32) return true;
     XArgs a = args;
     set_chunks(xprec, a);
     return a.nks > 1;
@@ -918,9 +1052,20 @@ hipError_t launch_xengine(int xprec, const XArgs &args, hipStream_t s) {
         case MWAX_X_FP16:
             hipLaunchKernelGGL(xengine_mfma<MWAX_X_FP16>, dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
             break;
-        case MWAX_X_FP32:
-            hipLaunchKernelGGL(xengine_f32, dim3((unsigned)blocks), dim3(kF32Threads), 0, s, a);
+        case MWAX_X_FP32: {
+            a.ntiles = xengine_tile_count(a.n_in, kFT);
+            const int64_t tiles = (int64_t)a.ntiles * a.L;
+            // fewer 64 x 64 tiles than the four per CU that are resident together
+            // would leave matrix cores idle; the small form has twice the waves per
+            // workgroup and up to four times the workgroups
+            if (tiles < 4 * device_cus()) {
+                a.ntiles = xengine_tile_count(a.n_in, 32);
+                hipLaunchKernelGGL(xengine_f32_small, dim3((unsigned)(a.ntiles * a.L)), dim3(64 * kFSWaves), 0, s, a);
+            } else {
+                hipLaunchKernelGGL(xengine_f32, dim3((unsigned)tiles), dim3(kThreads), 0, s, a);
+            }
             break;
+        }
         default:
             return hipErrorInvalidValue;
     }
