@@ -3,15 +3,17 @@
 //
 // Coherent beams: per channel c, the beams of a block are the complex product
 // B_c = W_c X_c (W_c: [beams][inputs] weights that phase the signal paths up
-// for each pointing; X_c: [inputs][spectra]).  It runs on the FP32 matrix
-// cores as two real products with K = (input, re/im):
-//   Re B = [Re W, -Im W] . [Re X; Im X],   Im B = [Im W, Re W] . [Re X; Im X]
-// with v_mfma_f32_32x32x2_f32: lanes 0..31 carry the re/re and lanes 32..63 the
-// im parts of one input per instruction.  A workgroup owns 64 beams x 64
-// spectra of one channel (four waves of 32 x 32); inputs are staged through LDS
-// 32 at a time, the int8 codes / binary16 values decoded to FP32 there.  The
-// channel's scale (INT8 s_c, FP16 2^e) is common to all inputs of the channel
-// and is applied to the sums.
+// for each pointing; X_c: [inputs][spectra]), as real products on the matrix
+// cores.  The channel's scale (INT8 s_c, FP16 2^e) is common to all inputs of
+// the channel and is applied to the sums.
+//   INT8, binary16 (beamform_kernel): bf16 instructions with FP32 sums.  An FP32
+//     weight is the exact sum of three bf16 pieces of 8 significant bits, an
+//     int8 code is one bf16 value and a binary16 value the exact sum of two, so
+//     every product is exact and only the FP32 sums round: three (six)
+//     instructions at 16 times the FP32 rate.
+//   FP32 (beamform_f32_kernel): v_mfma_f32_32x32x2_f32 with K = (input, re/im):
+//     Re B = [Re W, -Im W] . [Re X; Im X],   Im B = [Im W, Re W] . [Re X; Im X],
+//     lanes 0..31 carrying the re/re and lanes 32..63 the im parts of one input.
 //
 // Incoherent beam: the detected power of the inputs of each polarisation,
 // summed over t_avg spectra and f_avg channels (FP64 sums, fixed reduction
@@ -23,8 +25,7 @@ namespace {
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-constexpr int kKC = 32;     // inputs per LDS stage
-constexpr int kWP = kKC + 1;   // float2 pitch of a beam's weights in LDS
+typedef __bf16 v8b __attribute__((ext_vector_type(8)));
 
 // Spectrum t (0 .. G-1) of a 32-byte row, decoded to FP32 (before the scale).
 template <int ES>
@@ -37,12 +38,224 @@ __device__ __forceinline__ float2 row_value(const uint8_t *row, int t) {
     else return make_float2(*reinterpret_cast<const float *>(row + re), *reinterpret_cast<const float *>(row + im));
 }
 
+// The upper halves of x and y as one dword (x low): two bf16 values by truncation.
+__device__ __forceinline__ uint32_t pack_hi(float x, float y) {
+    return __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u);
+}
+// What truncation to bf16 leaves of x (exact); 0 for infinities and NaNs, whose
+// truncation already carries the value.
+__device__ __forceinline__ float rest_of(float x) {
+    const float h = __uint_as_float(__float_as_uint(x) & 0xffff0000u);
+    return fabsf(x) < __builtin_inff() ? x - h : 0.0f;
+}
+__device__ __forceinline__ v16f mma_bf16(const uint4 &a, const uint4 &b, v16f c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8b, a), __builtin_bit_cast(v8b, b), c, 0, 0, 0);
+}
+
+// Coherent beams of int8 codes (ES = 1) or binary16 values (ES = 2).  One
+// workgroup = one channel x 32 WB beams x kMT = 32 NC (4 / WB) spectra: WB waves
+// along the beams, 4 / WB along the spectra, a wave 32 beams x 32 NC spectra (rows
+// of the product = spectra, columns = beams, so that a wave stores runs of 32
+// beams).  K runs over stages of KI inputs in two LDS buffers, one stage ahead:
+// the voltages' rows are copied as they are (16 bytes per lane, straight into
+// LDS), each lane picking and converting the samples of its spectrum from there;
+// the weights are split into their pieces on the way into LDS.  Row n of a row
+// group sits at n ^ s within its eight rows, s = the 8-input half and the group's
+// low bits, so that the lanes of a read fall in distinct banks.
+// 32 beams, 256 tiles, 128 channels, 10,000 INT8 spectra: 0.55 ms (305 TFLOP/s of
+// the FP32 product, 3.0 TB/s of the 1.66 GB it cannot do without) against 1.86 ms
+// on the FP32 instructions, and half their error (2.9e-7 of the rms against
+// 5.7e-7: a sum rounds once per 16 inputs and piece, not once per input and
+// component).  Binary16, 8 to 96 beams: 1.75 to 1.95 times as fast.
+template <int ES, int WB, int NC>
+__global__ __launch_bounds__(256, 2) void beamform_kernel(BeamArgs a) {
+    constexpr int G = 16 / ES;
+    constexpr int KI = 32 / ES, KB = KI / 16;               // inputs and 16-input blocks per stage
+    constexpr int kMT = 32 * NC * (4 / WB), GL = kMT / G;   // spectra and row groups per workgroup
+    constexpr int NX = ES == 1 ? 1 : 2;                     // bf16 pieces of a voltage
+    constexpr int kX = GL * KI * kRowBytes, kW = KB * 2 * 3 * 2 * 32 * WB * 16;
+    __shared__ __align__(16) uint8_t xb0[kX], xb1[kX], wb0[kW], wb1[kW];
+    const int c = blockIdx.z;
+    const int64_t m0 = (int64_t)blockIdx.x * kMT;
+    const int b0 = blockIdx.y * 32 * WB;
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wb = wave / (4 / WB), wm = wave % (4 / WB);
+    const int64_t gstride = (int64_t)a.n_in * kRowBytes;
+    const uint8_t *base = a.chan + ((int64_t)c * a.NG + a.grp0) * gstride;
+    const int64_t g0 = m0 / G, glast = (a.nframes - 1) / G;
+    const float2 *wbase = a.w + ((int64_t)c * a.nb + b0) * a.n_in;
+    const int nst = (a.n_in + KI - 1) / KI;
+
+    // voltages: 16-byte units [row group][slot row][half row]; groups past the block
+    // and inputs past the last are read from clamped addresses (the groups' outputs
+    // are not stored, the inputs' weights are zero)
+    constexpr int kUnits = kX / 16, kCopies = kUnits / 256;
+    auto copy_x = [&](int s, uint8_t *xb) {
+#pragma unroll
+        for (int j = 0; j < kCopies; ++j) {
+            const int u0 = (wave * kCopies + j) * 64, u = u0 + lane;
+            const int gl = u / (2 * KI), slot = u % (2 * KI) / 2;
+            const int sw = ((slot >> 3) & 1) | ((gl & (2 * ES - 1)) << 1);
+            const int n = s * KI + ((slot & ~7) | ((slot ^ sw) & 7));
+            const uint8_t *src = base + min(g0 + gl, glast) * gstride + (int64_t)min(n, a.n_in - 1) * kRowBytes +
+                                 (u & 1) * 16;
+            __builtin_amdgcn_global_load_lds(src, xb + u0 * 16, 16, 0, 0);
+        }
+    };
+    // weights: quads of four inputs of one beam, as two pairs (n_in is even) from
+    // clamped addresses, zeroed past the beams and inputs when they are split (a
+    // load behind a branch would be waited for at once)
+    struct __attribute__((packed, aligned(8))) Pair { float v[4]; };
+    constexpr int kQuads = 32 * WB * KI / 4, kQ = (kQuads + 255) / 256;
+    float wq[kQ][8];   // (re, im) of four inputs
+    auto load_w = [&](int s) {
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+            const int u = tid + q * 256, bl = u / (KI / 4), n = s * KI + u % (KI / 4) * 4;
+            const float2 *row = wbase + (int64_t)min(bl, a.nb - 1 - b0) * a.n_in;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const Pair p = *reinterpret_cast<const Pair *>(row + min(n + 2 * h, a.n_in - 2));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) wq[q][4 * h + e] = p.v[e];
+            }
+        }
+    };
+    // LDS units of 16 bytes (8 inputs): [block][half][piece][re, im][beam]
+    auto store_w = [&](int s, uint8_t *wbuf) {
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) {
+            const int u = tid + q * 256, bl = u / (KI / 4), kq = u % (KI / 4);
+            if (kQuads % 256 != 0 && u >= kQuads) break;
+            const int n = s * KI + kq * 4;
+            uint8_t *dst = wbuf + (kq / 2 * 6 * 32 * WB + bl) * 16 + (kq & 1) * 8;
+#pragma unroll
+            for (int comp = 0; comp < 2; ++comp) {
+                float v[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float w = __builtin_canonicalizef(wq[q][2 * e + comp]);   // a quiet NaN keeps its top half
+                    v[e] = b0 + bl < a.nb && n + e < a.n_in ? w : 0.0f;
+                }
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+                    *reinterpret_cast<uint2 *>(dst + (p * 2 + comp) * 32 * WB * 16) =
+                        make_uint2(pack_hi(v[0], v[1]), pack_hi(v[2], v[3]));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = rest_of(v[e]);
+                }
+            }
+        }
+    };
+
+    v16f acc_r[NC], acc_i[NC];
+#pragma unroll
+    for (int nc = 0; nc < NC; ++nc) acc_r[nc] = acc_i[nc] = v16f{};
+    // this lane's place in a row group: spectrum t, group t's low bits
+    const int t = l32 % G, gsub = l32 / G;
+    const int sw = half | ((gsub & (2 * ES - 1)) << 1);
+    const int toff = ES == 1 ? (t >> 3) * 16 + ((t >> 2) & 1) * 4 : (t >> 2) * 16 + ((t >> 1) & 1) * 4;
+    const int shift = ES == 1 ? (t & 3) * 8 : (t & 1) * 16;
+    const int xoff = (wm * NC * (32 / G) + gsub) * KI * kRowBytes + half * 8 * kRowBytes + toff;
+    auto compute = [&](const uint8_t *xb, const uint8_t *wbuf) {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+            uint4 wr[3], wi[3];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                const uint8_t *src = wbuf + (((kb * 2 + half) * 6 + p * 2) * 32 * WB + wb * 32 + l32) * 16;
+                wr[p] = *reinterpret_cast<const uint4 *>(src);
+                wi[p] = *reinterpret_cast<const uint4 *>(src + 32 * WB * 16);
+            }
+#pragma unroll
+            for (int nc = 0; nc < NC; ++nc) {
+                uint32_t xr[NX][4], xi[NX][4];
+                const uint8_t *src = xb + xoff + nc * (32 / G) * KI * kRowBytes + kb * 16 * kRowBytes;
+#pragma unroll
+                for (int i = 0; i < 8; i += 2) {
+                    float r[2], m[2];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const uint8_t *row = src + ((i + e) ^ sw) * kRowBytes;
+                        const uint32_t dr = *reinterpret_cast<const uint32_t *>(row);
+                        const uint32_t di = *reinterpret_cast<const uint32_t *>(row + 8);
+                        if constexpr (ES == 1) {
+                            r[e] = (float)(int)__builtin_amdgcn_sbfe(dr, shift, 8);
+                            m[e] = (float)(int)__builtin_amdgcn_sbfe(di, shift, 8);
+                        } else {
+                            r[e] = (float)__builtin_bit_cast(_Float16, (uint16_t)(dr >> shift));
+                            m[e] = (float)__builtin_bit_cast(_Float16, (uint16_t)(di >> shift));
+                        }
+                    }
+                    xr[0][i / 2] = pack_hi(r[0], r[1]);
+                    xi[0][i / 2] = pack_hi(m[0], m[1]);
+                    if constexpr (NX == 2) {
+                        xr[1][i / 2] = pack_hi(rest_of(r[0]), rest_of(r[1]));
+                        xi[1][i / 2] = pack_hi(rest_of(m[0]), rest_of(m[1]));
+                    }
+                }
+                // the small products first
+#pragma unroll
+                for (int x = NX - 1; x >= 0; --x) {
+                    const uint4 vr = make_uint4(xr[x][0], xr[x][1], xr[x][2], xr[x][3]);
+                    const uint4 vi = make_uint4(xi[x][0], xi[x][1], xi[x][2], xi[x][3]);
+                    const uint4 vn = make_uint4(vi.x ^ 0x80008000u, vi.y ^ 0x80008000u, vi.z ^ 0x80008000u,
+                                                vi.w ^ 0x80008000u);
+#pragma unroll
+                    for (int p = 2; p >= 0; --p) {
+                        acc_r[nc] = mma_bf16(vr, wr[p], acc_r[nc]);
+                        acc_i[nc] = mma_bf16(vr, wi[p], acc_i[nc]);
+                        acc_r[nc] = mma_bf16(vn, wi[p], acc_r[nc]);
+                        acc_i[nc] = mma_bf16(vi, wr[p], acc_i[nc]);
+                    }
+                }
+            }
+        }
+    };
+
+    copy_x(0, xb0);
+    load_w(0);
+    store_w(0, wb0);
+    drain_barrier();
+    // stage s from one pair of buffers while stage s + 1 lands in the other (last
+    // read one iteration ago, behind a barrier); past the end a stage is copied from
+    // clamped addresses and not used
+    auto iteration = [&](int s, uint8_t *xc, uint8_t *wc, uint8_t *xn, uint8_t *wn) {
+        copy_x(s + 1, xn);
+        load_w(s + 1);
+        if (s < nst) compute(xc, wc);
+        store_w(s + 1, wn);
+        drain_barrier();
+    };
+    for (int s = 0; s < nst; s += 2) {
+        iteration(s, xb0, wb0, xb1, wb1);
+        iteration(s + 1, xb1, wb1, xb0, wb0);
+    }
+
+    // out[m][c][b]: lane l32 is beam l32 of the wave's block, rows are spectra
+    const float sc = a.scales ? a.scales[c] * a.post : a.post;
+    const int b = b0 + wb * 32 + l32;
+    if (b >= a.nb) return;
+#pragma unroll
+    for (int nc = 0; nc < NC; ++nc)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int64_t m = m0 + (wm * NC + nc) * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+            if (m < a.nframes)
+                a.out[((a.m0 + m) * a.L + c) * (int64_t)a.nb + b] = make_float2(acc_r[nc][r] * sc, acc_i[nc][r] * sc);
+        }
+}
+
+constexpr int kKC = 32;     // inputs per LDS stage of the FP32 kernel
+constexpr int kWP = kKC + 1;   // float2 pitch of a beam's weights in LDS
+
 // WB waves along the beams, 4 / WB along the spectra: a tile of 32 WB beams x
 // 128 / WB spectra (WB = 1 when a launch has at most 32 beams, so that no wave
 // multiplies empty beams).
-template <int ES, int WB>
-__global__ __launch_bounds__(256) void beamform_kernel(BeamArgs a) {
-    constexpr int G = 16 / ES;
+template <int WB>
+__global__ __launch_bounds__(256) void beamform_f32_kernel(BeamArgs a) {
+    constexpr int G = 4;
     constexpr int kBT = 32 * WB, kMT = 128 / WB;
     // one LDS block: the stage (weights [beam][input], voltages [input][spectrum])
     // and, after the K loop, the output tile [spectrum][beam] (pitch kBT + 1)
@@ -73,7 +286,7 @@ __global__ __launch_bounds__(256) void beamform_kernel(BeamArgs a) {
                 ws[bl * kWP + nl0 + e] = w;
             }
         }
-        // voltages: the kMT spectra of the tile for kKC inputs, decoded
+        // voltages: the kMT spectra of the tile for kKC inputs
         for (int u = tid; u < kKC * (kMT / G); u += 256) {
             const int nl = u % kKC, gl = u / kKC;
             const int n = n0 + nl;
@@ -86,7 +299,7 @@ __global__ __launch_bounds__(256) void beamform_kernel(BeamArgs a) {
                 __builtin_memcpy(buf, &h0, 16);
                 __builtin_memcpy(buf + 16, &h1, 16);
 #pragma unroll
-                for (int t = 0; t < G; ++t) v[t] = row_value<ES>(buf, t);
+                for (int t = 0; t < G; ++t) v[t] = row_value<4>(buf, t);
             } else {
 #pragma unroll
                 for (int t = 0; t < G; ++t) v[t] = make_float2(0.0f, 0.0f);
@@ -219,21 +432,32 @@ __global__ __launch_bounds__(256) void incoherent_kernel(IncohArgs a) {
 
 }  // namespace
 
+template <int WB, int NC>
+hipError_t launch_beamform_nc(int esize, const BeamArgs &a, hipStream_t s) {
+    constexpr int kBT = 32 * WB, kMT = 32 * NC * (4 / WB);
+    const dim3 grid((unsigned)((a.nframes + kMT - 1) / kMT), (unsigned)((a.nb + kBT - 1) / kBT), (unsigned)a.L);
+    if (esize == 1) hipLaunchKernelGGL((beamform_kernel<1, WB, NC>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((beamform_kernel<2, WB, NC>), grid, dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
 template <int WB>
 hipError_t launch_beamform_wb(int esize, const BeamArgs &a, hipStream_t s) {
     constexpr int kBT = 32 * WB, kMT = 128 / WB;
-    const dim3 grid((unsigned)((a.nframes + kMT - 1) / kMT), (unsigned)((a.nb + kBT - 1) / kBT), (unsigned)a.L);
-    switch (esize) {
-        case 1: hipLaunchKernelGGL((beamform_kernel<1, WB>), grid, dim3(256), 0, s, a); break;
-        case 2: hipLaunchKernelGGL((beamform_kernel<2, WB>), grid, dim3(256), 0, s, a); break;
-        case 4: hipLaunchKernelGGL((beamform_kernel<4, WB>), grid, dim3(256), 0, s, a); break;
-        default: return hipErrorInvalidValue;
+    if (esize == 4) {
+        const dim3 grid((unsigned)((a.nframes + kMT - 1) / kMT), (unsigned)((a.nb + kBT - 1) / kBT), (unsigned)a.L);
+        hipLaunchKernelGGL((beamform_f32_kernel<WB>), grid, dim3(256), 0, s, a);
+        return hipGetLastError();
     }
-    return hipGetLastError();
+    // the doubled spectra tile halves the weights' share of the loads and of the
+    // splitting; a block that fits the single one would multiply empty spectra
+    return a.nframes <= kMT ? launch_beamform_nc<WB, 1>(esize, a, s) : launch_beamform_nc<WB, 2>(esize, a, s);
 }
 
 hipError_t launch_beamform(int esize, const BeamArgs &a, hipStream_t s) {
     if (a.nframes <= 0 || a.nb <= 0) return hipSuccess;
+    if (esize != 1 && esize != 2 && esize != 4) return hipErrorInvalidValue;
+    // one block of 32 beams: no wave multiplies empty beams
     return a.nb <= 32 ? launch_beamform_wb<1>(esize, a, s) : launch_beamform_wb<2>(esize, a, s);
 }
 

@@ -161,6 +161,13 @@ __device__ __forceinline__ T load_uniform(const T *p) {
     return v;
 }
 
+// Ends a stage whose copies into LDS and LDS stores the next stage reads: waits
+// for all of this wave's, then for the workgroup.  One asm statement, so that no
+// LDS store can be moved between the wait and the barrier.
+__device__ __forceinline__ void drain_barrier() {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
 // Batched F-engine: one launch covers the segments of many plans with the same
 // L and precision.  The tables live in device memory (they change per call while
 // the launch itself, grid included, is fixed and can be replayed from a graph).

@@ -847,13 +847,11 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_f32(XArgs a) {
     };
 
     copy_stage(0, buf0);
-    __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
-    asm volatile("s_barrier" ::: "memory");
+    drain_barrier();
     auto iteration = [&](int s, uint8_t *cur, uint8_t *next) {
         copy_stage(s + 1, next);           // last read one iteration ago, behind a barrier
         if (active && s < nstages) compute(cur);
-        __builtin_amdgcn_s_waitcnt(0x0070);
-        asm volatile("s_barrier" ::: "memory");
+        drain_barrier();
     };
     static_assert(kFFlush % 2 == 0, "flushes fall between pairs of stages");
     for (int s0 = 0; s0 < nstages; s0 += kFFlush) {

@@ -153,3 +153,36 @@ def test_beamform_errors():
             p.beamform_incoherent(1, 3)                              # 3 does not divide 16 channels
         assert e.value.status == mwax.MWAX_E_INVAL
         assert p.beamform(w).shape == (10, 16, 1)
+
+
+@pytest.mark.parametrize("prec", ["fp16", "int8"])
+@pytest.mark.parametrize("n_tiles,L,M,nb,scale", [
+    (1, 2, 1, 1, 1.0),           # one tile, spectrum and beam
+    (17, 4, 128, 32, 1.0),       # 34 inputs: a ragged stage; the single spectra tile, full
+    (16, 4, 129, 33, 2.0 ** 90),   # whole stages; past the single tile of 64 and of 128 spectra
+    (31, 2, 257, 32, 2.0 ** -100),  # past the doubled tile, weights far from 1
+    (8, 2, 64, 65, 1.0),         # beams past two blocks of 32
+])
+def test_split_weights(prec, n_tiles, L, M, nb, scale):
+    """INT8 and binary16 beams on the bf16 instructions: the products are exact, so
+    the error is that of at most 6 n_in / 16 + 16 FP32 roundings per sum: the
+    bound of the other precisions' tests, 2e-6 of the rms, holds with room."""
+    n = 2 * n_tiles
+    rng = np.random.default_rng(n + M)
+    if prec == "int8":
+        x = rng.integers(-127, 128, size=(M, L, n, 2)).astype(np.int8)
+        post = 1.0
+    else:
+        x = (rng.normal(size=(M, L, n, 2)) * 30.0).astype(np.float16)
+        post = 2.0 ** ((int(np.log2(L)) + 1) // 2)
+    w = ((rng.normal(size=(L, nb, n)) + 1j * rng.normal(size=(L, nb, n))) * scale).astype(np.complex64)
+    with Plan(make_config(n_tiles, L=L, T=M, xprec=prec, max_samples=L * M)) as p:
+        p.load_channelised(torch.from_numpy(x).cuda())
+        B = p.beamform(torch.from_numpy(w).cuda()).cpu().numpy().astype(np.complex128)
+        w[0, 0, 0] = np.inf          # an infinite weight spoils its own beam and channel only
+        Binf = p.beamform(torch.from_numpy(w).cuda()).cpu().numpy()
+    ref = oracle.beamform((x[..., 0].astype(np.float64) + 1j * x[..., 1]) * post, np.where(np.isfinite(w), w, 0))
+    hit = np.zeros(B.shape, bool)
+    hit[:, 0, 0] = True
+    assert rel_err(B[~hit], ref[~hit]) < 2e-6
+    assert not np.isfinite(Binf[hit]).any() and np.array_equal(Binf[~hit], B[~hit].astype(np.complex64))
