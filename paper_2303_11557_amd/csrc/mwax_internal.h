@@ -162,9 +162,12 @@ __device__ __forceinline__ T load_uniform(const T *p) {
 }
 
 // Ends a stage whose copies into LDS and LDS stores the next stage reads: waits
-// for all of this wave's, then for the workgroup.  One asm statement, so that no
-// LDS store can be moved between the wait and the barrier.
+// for all of this wave's, then for the workgroup.  The wait in the asm is the one
+// that counts: no LDS store can be moved between it and the barrier.  The builtin
+// before it tells the compiler's own wait insertion that nothing is in flight any
+// more (without it the FP32 X-engine was 6 % slower).
 __device__ __forceinline__ void drain_barrier() {
+    __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
