@@ -106,14 +106,14 @@ struct FCfg {
     // inputs per item for FP32: 64-byte runs per channel).  Binary16 keeps one
     // frame per group (two would need 86 KB of LDS at L = 128, one workgroup per CU).
     static constexpr int FPG = XP == MWAX_X_INT8 ? (L >= 16 && L <= 256 ? 1 : 2) : 1;
-    // INT8 at L = 1024: four waves, each transforming two packs of an item in
-    // turn, its lanes loading their own samples straight from HBM (a lane's
-    // samples r + 64 n1 of a frame are one 128-byte line per load instruction).
-    // Without the staging area a workgroup needs 71 KB of LDS, so two fit a CU
-    // and one workgroup's barriers and image store overlap the other's FFTs:
-    // 2.34 instead of 1.86 TB/s.  (At L = 512, two 32-lane groups per wave,
-    // the same scheme ran at 2.04 instead of 2.37 TB/s.)
-    static constexpr bool DIRECT = XP == MWAX_X_INT8 && L == 1024;
+    // L = 1024: four waves whose lanes load their own samples straight from HBM (a
+    // lane's samples r + 64 n1 of a frame are one 128-byte line per load
+    // instruction), INT8 two packs of an item per wave in turn, binary16 two frames.
+    // Without the staging area two (INT8) or three workgroups fit a CU, and one's
+    // barriers and image store overlap the others' FFTs: INT8 2.34 instead of 1.86
+    // TB/s, binary16 and FP32 see SPLIT.  (At L = 512, two 32-lane groups per wave,
+    // INT8 ran at 2.04 instead of 2.37 TB/s this way.)
+    static constexpr bool DIRECT = L == 1024;
     static constexpr int THREADS = DIRECT ? kThreads : (L == 1024 ? 512 : kThreads);
     static constexpr int P = SH::P;
     static constexpr int GPW = 64 / L2;
@@ -123,14 +123,33 @@ struct FCfg {
     static constexpr int PPG = PACKS * R / NGWG;  // packs per group and item
     static constexpr int CP = R * kRowBytes + cp_pad(L, XP);
     static constexpr int SP = 2 * L + 16;         // staged frame pitch (bytes)
-    // exchange area per group (float2): L + 8, or L1 rows of L2 + P (P > 1)
+    // SPLIT: the lanes exchange the real and the imaginary parts one after the
+    // other through half the LDS (conflict-free as the float2 exchange is).  At L >=
+    // 128 binary16 and FP32, whose images are two and four times the INT8 one, then
+    // fit three workgroups on a CU instead of two (one at L = 1024): these launches
+    // wait for LDS and barriers (VALU 39 % busy), so a third wave per SIMD pays.
+    // 256 inputs x 0.5 s at L = 128 / 256 / 512 / 1024: binary16 388, 394, 553, 664
+    // -> 293, 339, 430, 422 us; 128 inputs FP32 217, 244, 274, 358 -> 188, 208,
+    // 249, 332 us.  INT8 has the third wave already (L <= 256) or cannot hold it in
+    // registers (L >= 512).
+    static constexpr bool SPLIT = XP != MWAX_X_INT8 && L >= 128;
+    // exchange area per group (float2, or float if SPLIT): L + L2 (8 at least, so
+    // that the groups of a wave start in distinct banks), or L1 rows of L2 + P (P > 1)
     static constexpr int EXR = L2 + P;
-    static constexpr int EXG = P > 1 ? L1 * EXR : L + 8;
+    static constexpr int EXG = P > 1 ? L1 * EXR : L + (SPLIT ? L2 : 8);
+    // ALIAS: a wave exchanges where its own staged frames were (each group
+    // transforms one frame per item, held in registers by then)
+    static constexpr bool ALIAS = SPLIT && FPG == 1 && PPG == 1 && !DIRECT;
+    static constexpr int WAVE_STAGE = GPW * SP, WAVE_EX = GPW * EXG * (SPLIT ? 4 : 8);
+    static constexpr int WAVE_PITCH = ALIAS ? (WAVE_STAGE > WAVE_EX ? WAVE_STAGE : (WAVE_EX + 15) / 16 * 16) : WAVE_STAGE;
     static constexpr int OUT_BYTES = L * CP;
-    static constexpr int STAGE_BYTES = L2 > 1 && !DIRECT ? R * G * SP : 0;
-    static constexpr int EX_BYTES = L2 > 1 ? NGWG * EXG * 8 : 0;
+    static constexpr int STAGE_BYTES = L2 > 1 && !DIRECT ? (ALIAS ? THREADS / 64 * WAVE_PITCH : R * G * SP) : 0;
+    static constexpr int EX_BYTES = L2 > 1 && !ALIAS ? THREADS / 64 * WAVE_EX : 0;
     // statistics pass: per-lane channel sums (L1 floats) and populated-frame counts
     static constexpr int RED_BYTES = THREADS * (L1 + 1) * 4;
+    // waves per SIMD the registers are held to (0: the compiler's choice); four
+    // would spill 7 to 15 registers and is slower (L = 256: 482 us)
+    static constexpr int MINW = SPLIT ? 3 : 0;
     // load the next item's frames while transforming the current one (where the
     // extra registers keep the occupancy)
     static constexpr bool PREFETCH = XP != MWAX_X_FP32 && L2 > 1 && (L <= 256 || XP == MWAX_X_INT8) && !DIRECT;
@@ -152,6 +171,36 @@ __device__ __forceinline__ float2 load_pair(const uint8_t *p) {
     return make_float2((float)((w << 8) >> 24), (float)(w >> 24));
 }
 
+// Exchange within one FFT group through its LDS area ex: dst[m] = the value some
+// lane holds as src[k] with write(k) == read(m).  SPLIT: real parts, then
+// imaginary parts, through an area of floats.  The caller orders it against
+// earlier and later uses of the area.
+template <bool SPLIT, int N, int M, class Write, class Read>
+__device__ __forceinline__ void lane_exchange(uint8_t *ex, const float2 (&src)[N], float2 (&dst)[M], Write &&write,
+                                              Read &&read) {
+    if constexpr (SPLIT) {
+        float *e = reinterpret_cast<float *>(ex);
+#pragma unroll
+        for (int k = 0; k < N; ++k) e[write(k)] = src[k].x;
+        wave_sync();
+#pragma unroll
+        for (int m = 0; m < M; ++m) dst[m].x = e[read(m)];
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < N; ++k) e[write(k)] = src[k].y;
+        wave_sync();
+#pragma unroll
+        for (int m = 0; m < M; ++m) dst[m].y = e[read(m)];
+    } else {
+        float2 *e = reinterpret_cast<float2 *>(ex);
+#pragma unroll
+        for (int k = 0; k < N; ++k) e[write(k)] = src[k];
+        wave_sync();
+#pragma unroll
+        for (int m = 0; m < M; ++m) dst[m] = e[read(m)];
+    }
+}
+
 // The work of workgroup wg of nwg workgroups on the segment described by a;
 // DELAY: apply the fractional delay and phase correction before requantising.
 template <int L, int XP, bool STATS, bool DELAY = false>
@@ -162,7 +211,12 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
     constexpr int GPW = C::GPW, PACKS = C::PACKS, R = C::R, CP = C::CP, SP = C::SP, EXG = C::EXG;
     uint8_t *outbuf = smem;
     uint8_t *stage = smem + (STATS ? 0 : C::OUT_BYTES);
-    float2 *ex = reinterpret_cast<float2 *>(stage + C::STAGE_BYTES);
+    uint8_t *exbase = stage + (C::ALIAS ? 0 : C::STAGE_BYTES);
+    // staged frame q = input slot G + f of the item
+    auto stage_at = [&](int q) {
+        if constexpr (C::ALIAS) return stage + q / GPW * C::WAVE_PITCH + q % GPW * SP;
+        else return stage + q * SP;
+    };
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int gi = lane / L2, r = lane % L2;
@@ -286,7 +340,7 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
                     const int sl = u / (G * UPF);
                     const int rem = u - sl * G * UPF;
                     const int f = rem / UPF, o = rem - f * UPF;
-                    *reinterpret_cast<uint4 *>(stage + (sl * G + f) * SP + o * 16) = pre[j];
+                    *reinterpret_cast<uint4 *>(stage_at(sl * G + f) + o * 16) = pre[j];
                 }
             }
             __syncthreads();
@@ -341,7 +395,7 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
                     for (int q = 0; q < L; ++q) v[q] = make_float2(0.0f, 0.0f);
                 }
             } else {
-                const uint8_t *fr = stage + (nl * G + f) * SP;
+                const uint8_t *fr = stage_at(nl * G + f);
 #pragma unroll
                 for (int n1 = 0; n1 < L1; ++n1) v[n1] = load_pair(fr + 2 * (r + L2 * n1));
             }
@@ -364,6 +418,16 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
 
             // this frame's delay (signal path n0 + nl) and phase offset
             float dl_alpha = 0.0f, dl_phi = 0.0f;
+            // CHAIN (binary16): a lane's bins of a column are evenly spaced, so its
+            // gains are a base times powers of the step between them: two sincos and
+            // a few products per frame instead of a sincos per bin.  The gains differ
+            // from the direct ones by at most a few 2^-24, a thousandth of the
+            // binary16 rounding that follows; INT8 and FP32, whose results would show
+            // it, evaluate every bin.  186 inputs, 1 s at L = 1024 with delays: 1330
+            // -> 875 us (with the third workgroup of SPLIT's comment).
+            constexpr bool CHAIN = DELAY && XP == MWAX_X_FP16 && L2 > 1;
+            constexpr int NT = P > 1 ? L1 : L2;          // bins of a column, evenly spaced
+            float2 pw[CHAIN ? NT / 2 + 1 : 1], gb[CHAIN && P == 1 ? U : 1];
             if constexpr (DELAY) {
                 float d = 0.0f;
                 if (nl < nrows && f < fvalid)
@@ -372,14 +436,38 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
                 dl_phi = (float)(ph - rint(ph));
                 dl_alpha = d * (1.0f / (float)L);
             }
+            auto make_gains = [&] {   // just before they are used: they live with the spectrum only
+                if constexpr (CHAIN) {
+#pragma unroll
+                for (int u = 0; u < (P == 1 ? U : 1); ++u)
+                    gb[u] = delay_gain(P > 1 ? bin_of<L, XP>(r, 0) : r * U + u, dl_alpha, dl_phi);
+                pw[0] = make_float2(1.0f, 0.0f);
+                pw[1] = delay_gain(L / NT, dl_alpha, 0.0f);
+#pragma unroll
+                for (int t = 2; t <= NT / 2; ++t) {   // products of the two halves of t: few roundings
+                    const float2 x = pw[t / 2], y = pw[t - t / 2];
+                    pw[t] = make_float2(x.x * y.x - x.y * y.y, x.x * y.y + x.y * y.x);
+                }
+                }
+            };
 
             // consume output slot i (FFT bin of this lane) with value X; tc: the
             // frame's place in its pack as a compile-time constant (see emit_frame)
             auto emit = [&](int i, float2 X, auto tc) {
                 constexpr int T = decltype(tc)::value;
                 if constexpr (DELAY) {
-                    const int k = bin_of<L, XP>(r, i);
-                    const float2 g = delay_gain(k < L / 2 ? k : k - L, dl_alpha, dl_phi);
+                    float2 g;
+                    if constexpr (CHAIN) {
+                        // slot i is bin t of its column; the upper half are the negative
+                        // frequencies t - NT, conjugate powers
+                        const int t = P > 1 ? i / P + L1 / P * (i % P) : i % L2;
+                        const float2 w = t < NT / 2 ? pw[t] : make_float2(pw[NT - t].x, -pw[NT - t].y);
+                        const float2 c = gb[P > 1 ? 0 : i / L2];
+                        g = make_float2(c.x * w.x - c.y * w.y, c.x * w.y + c.y * w.x);
+                    } else {
+                        const int k = bin_of<L, XP>(r, i);
+                        g = delay_gain(k < L / 2 ? k : k - L, dl_alpha, dl_phi);
+                    }
                     X = make_float2(X.x * g.x - X.y * g.y, X.x * g.y + X.y * g.x);
                 }
                 if constexpr (STATS) {
@@ -454,6 +542,8 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
                     else w = a.tw[(r * k1) % L];
                     v[k1] = make_float2(v[k1].x * w.x - v[k1].y * w.y, v[k1].x * w.y + v[k1].y * w.x);
                 }
+                uint8_t *eg = exbase + (C::ALIAS ? wave * C::WAVE_PITCH + gi * EXG * 4 : gg * EXG * (C::SPLIT ? 4 : 8));
+                if constexpr (C::ALIAS) wave_sync();   // the wave's frames have been read
                 if constexpr (P > 1) {
                     // lane r writes its column of the L1 x L2 block (row pitch
                     // L2 + P keeps the writes and the strided reads below free of
@@ -463,36 +553,33 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
                     // columns m2 = g + P j; each takes the twiddle W_L2^(h m2) (none
                     // for h = 0) and their P-point DFTs complete the column's
                     // transform: slot j P + q of the lane holds bin k1 + L1 (g + P j + L1 q)
-                    float2 *eg = ex + gg * EXG;
-#pragma unroll
-                    for (int k1 = 0; k1 < L1; ++k1) eg[k1 * C::EXR + r] = v[k1];
-                    wave_sync();
                     const int k1 = r / P, h = r % P;
                     float2 w[L1];
-#pragma unroll
-                    for (int m = 0; m < L1; ++m) w[m] = eg[k1 * C::EXR + h + P * m];
+                    lane_exchange<C::SPLIT>(eg, v, w, [&](int k) { return k * C::EXR + r; },
+                                            [&](int m) { return k1 * C::EXR + h + P * m; });
                     dft_regs<L1>(w);
-                    // lane rows of L1 + 1 float2: writes (fixed m) and reads (fixed
+                    // lane rows of L1 + 1 values: writes (fixed m) and reads (fixed
                     // h, j) both fall in distinct banks
                     constexpr int XR = L1 + 1;
                     static_assert(C::L2 * XR <= EXG, "second exchange exceeds the group's area");
                     wave_sync();   // the first exchange has been read
-#pragma unroll
-                    for (int m = 0; m < L1; ++m) eg[r * XR + m] = w[m];
-                    wave_sync();
+                    float2 y[L1];
+                    lane_exchange<C::SPLIT>(eg, w, y, [&](int m) { return r * XR + m; },
+                                            [&](int i) { return (k1 * P + i % P) * XR + h + P * (i / P); });
 #pragma unroll
                     for (int j = 0; j < L1 / P; ++j) {
 #pragma unroll
                         for (int q = 0; q < P; ++q) {
-                            float2 y = eg[(k1 * P + q) * XR + h + P * j];
+                            float2 u = y[j * P + q];
                             if (q > 0) {
                                 const float2 t = tw2[(q - 1) * (L1 / P) + j];
-                                y = make_float2(y.x * t.x - y.y * t.y, y.x * t.y + y.y * t.x);
+                                u = make_float2(u.x * t.x - u.y * t.y, u.x * t.y + u.y * t.x);
                             }
-                            w[j * P + q] = y;
+                            w[j * P + q] = u;
                         }
                         dft_regs<P>(w + j * P);
                     }
+                    make_gains();
                     emit_frame([&](auto tc) {
 #pragma unroll
                         for (int i = 0; i < L1; ++i) emit(i, w[i], tc);
@@ -500,21 +587,39 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
                 } else {
                     // exchange through LDS; column swizzle r ^ (k1 / U) keeps both the
                     // writes (fixed k1) and the reads (fixed r2) free of bank conflicts
-                    float2 *eg = ex + gg * EXG;
+                    // (all U columns of a lane are read before their transforms if
+                    // the parts are exchanged in turn)
+                    if constexpr (C::SPLIT) {
+                        float2 w[U * L2];
+                        lane_exchange<true>(eg, v, w, [&](int k) { return k * L2 + (r ^ (k / U)); },
+                                            [&](int m) { return (r * U + m / L2) * L2 + (m % L2 ^ r); });
+                        make_gains();
 #pragma unroll
-                    for (int k1 = 0; k1 < L1; ++k1) eg[k1 * L2 + (r ^ (k1 / U))] = v[k1];
-                    wave_sync();
+                        for (int u = 0; u < U; ++u) {
+                            dft_regs<L2>(w + u * L2);
+                            emit_frame([&](auto tc) {
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const int k1 = r * U + u;
-                        float2 w[L2];
+                                for (int k2 = 0; k2 < L2; ++k2) emit(u * L2 + k2, w[u * L2 + k2], tc);
+                            });
+                        }
+                    } else {
+                        float2 *e = reinterpret_cast<float2 *>(eg);
 #pragma unroll
-                        for (int r2 = 0; r2 < L2; ++r2) w[r2] = eg[k1 * L2 + (r2 ^ r)];
-                        dft_regs<L2>(w);
-                        emit_frame([&](auto tc) {
+                        for (int k1 = 0; k1 < L1; ++k1) e[k1 * L2 + (r ^ (k1 / U))] = v[k1];
+                        make_gains();
+                        wave_sync();
 #pragma unroll
-                            for (int k2 = 0; k2 < L2; ++k2) emit(u * L2 + k2, w[k2], tc);
-                        });
+                        for (int u = 0; u < U; ++u) {
+                            const int k1 = r * U + u;
+                            float2 w[L2];
+#pragma unroll
+                            for (int r2 = 0; r2 < L2; ++r2) w[r2] = e[k1 * L2 + (r2 ^ r)];
+                            dft_regs<L2>(w);
+                            emit_frame([&](auto tc) {
+#pragma unroll
+                                for (int k2 = 0; k2 < L2; ++k2) emit(u * L2 + k2, w[k2], tc);
+                            });
+                        }
                     }
                 }
                 wave_sync();
@@ -576,7 +681,7 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
 }
 
 template <int L, int XP, bool STATS, bool DELAY>
-__global__ __launch_bounds__((FCfg<L, XP>::THREADS)) void fengine_kernel(FArgs a) {
+__global__ __launch_bounds__((FCfg<L, XP>::THREADS), (STATS || (DELAY && (XP != MWAX_X_FP16 || L == 1024)) ? 1 : std::max(1, FCfg<L, XP>::MINW))) void fengine_kernel(FArgs a) {
     extern __shared__ __align__(16) uint8_t smem[];
     fengine_body<L, XP, STATS, DELAY>(a, blockIdx.x, gridDim.x, 0, smem);
 }
