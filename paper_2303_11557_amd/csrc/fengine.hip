@@ -171,34 +171,24 @@ __device__ __forceinline__ float2 load_pair(const uint8_t *p) {
     return make_float2((float)((w << 8) >> 24), (float)(w >> 24));
 }
 
-// Exchange within one FFT group through its LDS area ex: dst[m] = the value some
-// lane holds as src[k] with write(k) == read(m).  SPLIT: real parts, then
-// imaginary parts, through an area of floats.  The caller orders it against
-// earlier and later uses of the area.
-template <bool SPLIT, int N, int M, class Write, class Read>
-__device__ __forceinline__ void lane_exchange(uint8_t *ex, const float2 (&src)[N], float2 (&dst)[M], Write &&write,
-                                              Read &&read) {
-    if constexpr (SPLIT) {
-        float *e = reinterpret_cast<float *>(ex);
+// Exchange within one FFT group through its LDS area of floats ex, real parts,
+// then imaginary parts: dst[m] = the value some lane holds as src[k] with write(k)
+// == read(m).  The caller orders it against earlier and later uses of the area.
+template <int N, int M, class Write, class Read>
+__device__ __forceinline__ void split_exchange(uint8_t *ex, const float2 (&src)[N], float2 (&dst)[M], Write &&write,
+                                               Read &&read) {
+    float *e = reinterpret_cast<float *>(ex);
 #pragma unroll
-        for (int k = 0; k < N; ++k) e[write(k)] = src[k].x;
-        wave_sync();
+    for (int k = 0; k < N; ++k) e[write(k)] = src[k].x;
+    wave_sync();
 #pragma unroll
-        for (int m = 0; m < M; ++m) dst[m].x = e[read(m)];
-        wave_sync();
+    for (int m = 0; m < M; ++m) dst[m].x = e[read(m)];
+    wave_sync();
 #pragma unroll
-        for (int k = 0; k < N; ++k) e[write(k)] = src[k].y;
-        wave_sync();
+    for (int k = 0; k < N; ++k) e[write(k)] = src[k].y;
+    wave_sync();
 #pragma unroll
-        for (int m = 0; m < M; ++m) dst[m].y = e[read(m)];
-    } else {
-        float2 *e = reinterpret_cast<float2 *>(ex);
-#pragma unroll
-        for (int k = 0; k < N; ++k) e[write(k)] = src[k];
-        wave_sync();
-#pragma unroll
-        for (int m = 0; m < M; ++m) dst[m] = e[read(m)];
-    }
+    for (int m = 0; m < M; ++m) dst[m].y = e[read(m)];
 }
 
 // The work of workgroup wg of nwg workgroups on the segment described by a;
@@ -553,31 +543,60 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
                     // columns m2 = g + P j; each takes the twiddle W_L2^(h m2) (none
                     // for h = 0) and their P-point DFTs complete the column's
                     // transform: slot j P + q of the lane holds bin k1 + L1 (g + P j + L1 q)
+                    // (the two forms compile to differently contracted products: INT8, whose
+                    // codes and scales would show it, keeps the one it always had)
                     const int k1 = r / P, h = r % P;
-                    float2 w[L1];
-                    lane_exchange<C::SPLIT>(eg, v, w, [&](int k) { return k * C::EXR + r; },
-                                            [&](int m) { return k1 * C::EXR + h + P * m; });
-                    dft_regs<L1>(w);
-                    // lane rows of L1 + 1 values: writes (fixed m) and reads (fixed
-                    // h, j) both fall in distinct banks
+                    // lane rows of L1 + 1 values in the second exchange: writes (fixed m)
+                    // and reads (fixed h, j) both fall in distinct banks
                     constexpr int XR = L1 + 1;
                     static_assert(C::L2 * XR <= EXG, "second exchange exceeds the group's area");
-                    wave_sync();   // the first exchange has been read
-                    float2 y[L1];
-                    lane_exchange<C::SPLIT>(eg, w, y, [&](int m) { return r * XR + m; },
-                                            [&](int i) { return (k1 * P + i % P) * XR + h + P * (i / P); });
+                    float2 w[L1];
+                    if constexpr (C::SPLIT) {
+                        split_exchange(eg, v, w, [&](int k) { return k * C::EXR + r; },
+                                       [&](int m) { return k1 * C::EXR + h + P * m; });
+                        dft_regs<L1>(w);
+                        wave_sync();   // the first exchange has been read
+                        float2 y[L1];
+                        split_exchange(eg, w, y, [&](int m) { return r * XR + m; },
+                                       [&](int i) { return (k1 * P + i % P) * XR + h + P * (i / P); });
 #pragma unroll
-                    for (int j = 0; j < L1 / P; ++j) {
+                        for (int j = 0; j < L1 / P; ++j) {
 #pragma unroll
-                        for (int q = 0; q < P; ++q) {
-                            float2 u = y[j * P + q];
-                            if (q > 0) {
-                                const float2 t = tw2[(q - 1) * (L1 / P) + j];
-                                u = make_float2(u.x * t.x - u.y * t.y, u.x * t.y + u.y * t.x);
+                            for (int q = 0; q < P; ++q) {
+                                float2 u = y[j * P + q];
+                                if (q > 0) {
+                                    const float2 t = tw2[(q - 1) * (L1 / P) + j];
+                                    u = make_float2(u.x * t.x - u.y * t.y, u.x * t.y + u.y * t.x);
+                                }
+                                w[j * P + q] = u;
                             }
-                            w[j * P + q] = u;
+                            dft_regs<P>(w + j * P);
                         }
-                        dft_regs<P>(w + j * P);
+                    } else {
+                        float2 *e = reinterpret_cast<float2 *>(eg);
+#pragma unroll
+                        for (int k = 0; k < L1; ++k) e[k * C::EXR + r] = v[k];
+                        wave_sync();
+#pragma unroll
+                        for (int m = 0; m < L1; ++m) w[m] = e[k1 * C::EXR + h + P * m];
+                        dft_regs<L1>(w);
+                        wave_sync();   // the first exchange has been read
+#pragma unroll
+                        for (int m = 0; m < L1; ++m) e[r * XR + m] = w[m];
+                        wave_sync();
+#pragma unroll
+                        for (int j = 0; j < L1 / P; ++j) {
+#pragma unroll
+                            for (int q = 0; q < P; ++q) {
+                                float2 y = e[(k1 * P + q) * XR + h + P * j];
+                                if (q > 0) {
+                                    const float2 t = tw2[(q - 1) * (L1 / P) + j];
+                                    y = make_float2(y.x * t.x - y.y * t.y, y.x * t.y + y.y * t.x);
+                                }
+                                w[j * P + q] = y;
+                            }
+                            dft_regs<P>(w + j * P);
+                        }
                     }
                     make_gains();
                     emit_frame([&](auto tc) {
@@ -591,8 +610,8 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
                     // the parts are exchanged in turn)
                     if constexpr (C::SPLIT) {
                         float2 w[U * L2];
-                        lane_exchange<true>(eg, v, w, [&](int k) { return k * L2 + (r ^ (k / U)); },
-                                            [&](int m) { return (r * U + m / L2) * L2 + (m % L2 ^ r); });
+                        split_exchange(eg, v, w, [&](int k) { return k * L2 + (r ^ (k / U)); },
+                                       [&](int m) { return (r * U + m / L2) * L2 + (m % L2 ^ r); });
                         make_gains();
 #pragma unroll
                         for (int u = 0; u < U; ++u) {
