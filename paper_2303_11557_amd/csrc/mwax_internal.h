@@ -230,31 +230,43 @@ struct XArgs {
                             // non-atomic flush stores instead of adding
     int32_t i32;            // INT8 integrators are int32 pairs (else int64)
 };
-// Averaging X-engine (plans with mwax_set_averaging): one segment of F-channel
+// Segments of a block that one launch works on (FP32 and averaging X-engines):
+// the last, partly filled round of workgroups is then paid once per call.
+constexpr int kXSegs = 8;
+struct XSeg {
+    int64_t grp0;           // first group of the segment
+    void *integ;            // its slot's integrators
+    const float *scales;    // averaging, INT8: s_c [L] of its integration; else NULL
+    int32_t ngrp;           // groups in the segment
+    int32_t first;          // the segment starts its integration: store, not add
+};
+struct XSegList {
+    XSeg s[kXSegs];
+    int32_t n;
+};
+// FP32 X-engine; a: as launch_xengine but for the fields of the segments.
+hipError_t launch_xengine_f32(const XArgs &a, const XSegList &segs, hipStream_t s);
+// Averaging X-engine (plans with mwax_set_averaging): segments of F-channel
 // output channels, accumulated straight into FP64 integrators [N][P][2].
 struct XAvgArgs {
     const uint8_t *chan;    // [L][NG][N_in][32 B]
     int64_t NG;
-    int64_t grp0;           // first group of the segment
-    int32_t ngrp;           // groups in the segment
     int32_t n_in;
     int32_t L;
     int32_t F;              // fine channels per output channel
     int32_t N;              // output channels, L / F
     int32_t ntiles;         // 64-edge lower-triangle tiles per channel
-    const float *scales;    // INT8: s_c [L] of the segment's integration; else NULL
-    void *integ;            // this slot's integrators [N][P] (double2)
     int64_t P;
-    int32_t first;          // the segment starts its integration: store, not add
+    XSegList segs;          // integrators: [N][P] (double2)
 };
 hipError_t launch_xengine_avg(int xprec, const XAvgArgs &a, hipStream_t s);
 
-// INT8 launches split every tile's row groups into chunks when that fills the
-// device's resident workgroup slots more evenly (chunks flush with exact int64
-// atomic adds); other precisions run whole segments.
+// INT8 and FP16.  INT8 launches split every tile's row groups into chunks when
+// that fills the device's resident workgroup slots more evenly (chunks flush with
+// exact int64 atomic adds); FP16 runs whole segments.
 hipError_t launch_xengine(int xprec, const XArgs &a, hipStream_t s);
-// True if launch_xengine adds every partial sum into the integrators (FP32, or
-// INT8 split into chunks); false if the first flush of a segment that starts
+// True if launch_xengine adds every partial sum into the integrators (INT8 split
+// into chunks); false if the first flush of a segment that starts
 // its integration overwrites them.
 bool xengine_accumulates(int xprec, const XArgs &a);
 int xengine_tile(int xprec);
@@ -315,6 +327,8 @@ struct PackArgs {
     float *scales_out;      // raw mode: copy of s_c, may be NULL
     int32_t order;          // mwax_order; 2 = raw int64; 3 = averaged by F (CHAN_TRI)
     int32_t clear;          // zero the integrators after reading them
+    int32_t fix_im;         // FP64 integrators of INT8 codes (averaging X-engine): subtract
+                            // the row's auto from the imaginary parts
     int32_t i32;            // INT8 integrators are int32 pairs (else int64)
     int32_t L;
     int32_t n_in;

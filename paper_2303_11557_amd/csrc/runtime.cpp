@@ -634,28 +634,43 @@ mwax_status mwax_beamform_incoherent(mwax_plan p, int32_t t_avg, int32_t f_avg, 
 mwax_status mwax_correlate(mwax_plan p) {
     if (check_plan(p) != MWAX_OK) return MWAX_E_INVAL;
     if (!p->pending) return fail(MWAX_E_STATE, "no fresh channelised block to correlate");
-    for (const Segment &s : p->segs) {
-        if (p->favg > 1) {
-            // averaging X-engine: whole segments, the first one of an integration stores
-            XAvgArgs v{};
-            v.chan = p->chan;
-            v.NG = p->NG;
-            v.grp0 = s.grp0;
-            v.ngrp = (int32_t)s.ngrp;
-            v.n_in = p->n_in;
-            v.L = p->L;
-            v.F = p->favg;
-            v.N = p->L / p->favg;
-            v.ntiles = xengine_tile_count(p->n_in, kXTileSmall);
-            v.scales = p->xprec == MWAX_X_INT8 ? p->scales + (size_t)s.slot * 2 * p->L : nullptr;
-            v.integ = (uint8_t *)p->integ + (size_t)s.slot * p->slot_bytes;
-            v.P = p->P;
-            v.first = s.local0 == 0;
-            hipError_t e = timed(p, 1, [&] { return launch_xengine_avg(p->xprec, v, p->stream); });
+    // Averaging and FP32 X-engines: the block's segments (each in a slot of its own)
+    // in launches of up to kXSegs; whole segments, the first one of an integration
+    // stores.
+    if (p->favg > 1 || p->xprec == MWAX_X_FP32) {
+        // a launch holds at most 2^32 - 1 threads, 256 per (segment, channel, tile)
+        const int64_t per_seg = (int64_t)xengine_tile_count(p->n_in, kXTileSmall) * (p->L / p->favg) * 256;
+        const size_t step = (size_t)std::max<int64_t>(1, std::min<int64_t>(kXSegs, UINT32_MAX / per_seg));
+        for (size_t k0 = 0; k0 < p->segs.size(); k0 += step) {
+            XSegList q{};
+            q.n = (int32_t)std::min(step, p->segs.size() - k0);
+            for (int k = 0; k < q.n; ++k) {
+                const Segment &s = p->segs[k0 + k];
+                q.s[k] = {s.grp0, (uint8_t *)p->integ + (size_t)s.slot * p->slot_bytes,
+                          p->xprec == MWAX_X_INT8 ? p->scales + (size_t)s.slot * 2 * p->L : nullptr, (int32_t)s.ngrp,
+                          s.local0 == 0};
+            }
+            hipError_t e = timed(p, 1, [&] {
+                if (p->favg == 1) return launch_xengine_f32(xengine_args(p, p->segs[k0]), q, p->stream);
+                XAvgArgs v{};
+                v.chan = p->chan;
+                v.NG = p->NG;
+                v.n_in = p->n_in;
+                v.L = p->L;
+                v.F = p->favg;
+                v.N = p->L / p->favg;
+                v.ntiles = xengine_tile_count(p->n_in, kXTileSmall);
+                v.P = p->P;
+                v.segs = q;
+                return launch_xengine_avg(p->xprec, v, p->stream);
+            });
             if (e != hipSuccess) return hip_fail(e, "X-engine launch");
-            p->slot_count[s.slot] += s.nframes;
-            continue;
+            for (int k = 0; k < q.n; ++k) p->slot_count[p->segs[k0 + k].slot] += p->segs[k0 + k].nframes;
         }
+        p->pending = false;
+        return ok();
+    }
+    for (const Segment &s : p->segs) {
         const XArgs a = xengine_args(p, s);
         if (s.local0 == 0 && !p->clear_on_emit && xengine_accumulates(p->xprec, a)) {
             // this launch adds into a slot that was not cleared when it was last emitted
@@ -693,6 +708,7 @@ static mwax_status emit(mwax_plan p, void *d_vis, float *d_scales, int32_t max_i
         a.scales_out = d_scales ? d_scales + (size_t)n * p->L : nullptr;
         a.order = order;
         a.clear = p->clear_on_emit && !pre;
+        a.fix_im = 0;
         a.i32 = p->integ32;
         a.L = pre ? p->L / p->favg : p->L;
         a.n_in = p->n_in;

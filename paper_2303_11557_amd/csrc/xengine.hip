@@ -545,11 +545,11 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
     uint8_t *const bufs[4] = {lds0, lds1, lds2, lds3};
     static_assert(kNBuf == 4, "four stage buffers");
 
-    const int nb = gridDim.x;
-    const int lin = xcd_logical(blockIdx.x, nb);
-    const int o = lin / a.ntiles;
+    const int lin = xcd_logical(blockIdx.x, gridDim.x);
+    const int os = lin / a.ntiles, seg = os / a.N, o = os - seg * a.N;
+    const XSeg sg = a.segs.s[seg];
     int I, J;
-    tile_ij(lin - o * a.ntiles, I, J);
+    tile_ij(lin - os * a.ntiles, I, J);
     const int rowA0 = I * TE, rowB0 = J * TE;
     const int lane = threadIdx.x & 63;
     const int half = lane >> 5, l32 = lane & 31;
@@ -581,27 +581,27 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
     const int64_t gstride = (int64_t)a.n_in * kRowBytes;
     const int64_t cstride = a.NG * gstride;       // bytes between channels
     const int ldst = cpanel + cblk * kBlock;
-    const int spc = (a.ngrp + kXG - 1) / kXG;     // stages per channel
+    const int spc = (sg.ngrp + kXG - 1) / kXG;     // stages per channel
     const int nst = nch * spc;
 
     // copy cursor: channel index, its channel and offset, stage within it, and the
     // address of the stage's first row group
     int cp_ci = 0, cp_c = c_first, cp_d = -h, cp_g = 0;
     if (centre && cp_d == 0) cp_d = 1;            // (h = 0 only when F = 1: no centre rule)
-    const uint8_t *cp_base = a.chan + ((int64_t)cp_c * a.NG + a.grp0) * gstride;
+    const uint8_t *cp_base = a.chan + ((int64_t)cp_c * a.NG + sg.grp0) * gstride;
     const uint8_t *cp_src = cp_base;
     const int64_t stage_bytes = (int64_t)kXG * gstride;
     auto copy_next = [&](uint8_t *buf) {
         const bool live = cp_ci < nch;
 #pragma unroll
         for (int k = 0; k < kXG; ++k) {
-            const bool in = live && cp_g + k < a.ngrp;
+            const bool in = live && cp_g + k < sg.ngrp;
             const uint8_t *src = in ? cp_src + k * gstride + offR : kZeroGroup + offZ;
             __builtin_amdgcn_global_load_lds(src, buf + k * kGroupPitch + ldst, 16, 0, 0);
         }
         cp_g += kXG;
         cp_src += stage_bytes;
-        if (cp_g >= a.ngrp) {
+        if (cp_g >= sg.ngrp) {
             cp_g = 0;
             ++cp_ci;
             const int nc = next_channel(cp_c, cp_d);
@@ -650,8 +650,8 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
             const int d = -h + ci + (centre && ci >= h ? 1 : 0);
             const int c = (((a.L / 2 + (o - oc) * a.F + d) % a.L) + a.L) % a.L;
             float coef = (even && (d == -h || d == h) ? 0.5f : 1.0f) * inv_wsum;
-            if (a.scales && ci < nch) {
-                const float sc = a.scales[c];
+            if (sg.scales && ci < nch) {
+                const float sc = sg.scales[c];
                 coef *= sc * sc;
             }
             ctab[t] = coef;
@@ -698,7 +698,7 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
     __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0): copies past the end have landed
 
     if (active) {
-        double2 *dst0 = reinterpret_cast<double2 *>(a.integ) + (int64_t)o * a.P;
+        double2 *dst0 = reinterpret_cast<double2 *>(sg.integ) + (int64_t)o * a.P;
         const int n2 = rowB0 + wc * 32 + l32;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
@@ -706,7 +706,7 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
             if (n1 < a.n_in && n2 <= n1) {
                 double2 *dst = dst0 + (int64_t)n1 * (n1 + 1) / 2 + n2;
                 double2 v = make_double2((double)sr[r], (double)si[r]);
-                if (!a.first) {
+                if (!sg.first) {
                     const double2 old = *dst;
                     v.x += old.x;
                     v.y += old.y;
@@ -768,13 +768,13 @@ __device__ __forceinline__ void mma_f32_group(float4 a, float4 b, float4 b2, uin
 // the flushes): 256 inputs, 128 channels, 5,000 spectra take 1.7-1.8 ms, 96
 // TFLOP/s of the 151 a large library product reaches, where 4 x 8 outputs per
 // thread on the vector ALUs took 4.6 ms.
-__global__ __launch_bounds__(kThreads, 4) void xengine_f32(XArgs a) {
+__global__ __launch_bounds__(kThreads, 4) void xengine_f32(XArgs a, XSegList segs) {
     __shared__ __align__(16) uint8_t buf0[kFStage], buf1[kFStage];
-    const int nb = gridDim.x;
-    const int lin = xcd_logical(blockIdx.x, nb);
-    const int c = lin / a.ntiles;
+    const int lin = xcd_logical(blockIdx.x, gridDim.x);
+    const int cs = lin / a.ntiles, seg = cs / a.L, c = cs - seg * a.L;
+    const XSeg sg = segs.s[seg];
     int I, J;
-    tile_ij(lin - c * a.ntiles, I, J);
+    tile_ij(lin - cs * a.ntiles, I, J);
     const int rowA0 = I * kFT, rowB0 = J * kFT;
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -790,14 +790,14 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_f32(XArgs a) {
     const uint32_t offR = (uint32_t)min((wave < 2 ? rowA0 : rowB0) + crow, a.n_in - 1) * kRowBytes + half * 16;
     const uint32_t offZ = (uint32_t)crow * kRowBytes + half * 16;
     const int64_t gstride = (int64_t)a.n_in * kRowBytes;
-    const uint8_t *base = a.chan + ((int64_t)c * a.NG + a.grp0) * gstride;
+    const uint8_t *base = a.chan + ((int64_t)c * a.NG + sg.grp0) * gstride;
     const int ldst = (wave >> 1) * kFPanel + cblk * kBlock;
-    const int nstages = (a.ngrp + kFG - 1) / kFG;
+    const int nstages = (sg.ngrp + kFG - 1) / kFG;
     auto copy_stage = [&](int s, uint8_t *buf) {
 #pragma unroll
         for (int k = 0; k < kFG; ++k) {
             const int g = s * kFG + k;
-            const uint8_t *src = g < a.ngrp ? base + g * gstride + offR : kZeroGroup + offZ;
+            const uint8_t *src = g < sg.ngrp ? base + g * gstride + offR : kZeroGroup + offZ;
             __builtin_amdgcn_global_load_lds(src, buf + k * kFGroup + ldst, 16, 0, 0);
         }
     };
@@ -819,13 +819,13 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_f32(XArgs a) {
     };
     // the outer sums into the FP64 integrators; the first flush of a segment that
     // starts its integration stores instead of adding
-    bool store = a.first != 0;
+    bool store = sg.first != 0;
     auto flush = [&]() {
         // opaque, so that the 16 addresses are not formed ahead of the K loop and
         // held in registers through it
         int fr0 = rowA0 + wr * 32, fc0 = rowB0 + wc * 32;
         asm volatile("" : "+s"(fr0), "+s"(fc0));
-        double2 *dst0 = reinterpret_cast<double2 *>(a.integ) + (int64_t)c * a.P;
+        double2 *dst0 = reinterpret_cast<double2 *>(sg.integ) + (int64_t)c * a.P;
         const int n2 = fc0 + l32;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
@@ -873,32 +873,32 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_f32(XArgs a) {
 // 1,000 spectra: a 535 us step became 38 us (one 128-edge workgroup per channel
 // ran its 63 stages one after another on half of the CUs).
 constexpr int kFSWaves = 8;
-__global__ __launch_bounds__(64 * kFSWaves, 2) void xengine_f32_small(XArgs a) {
+__global__ __launch_bounds__(64 * kFSWaves, 2) void xengine_f32_small(XArgs a, XSegList segs) {
     __shared__ double2 part[kFSWaves / 2][16][64];
-    const int nb = gridDim.x;
-    const int lin = xcd_logical(blockIdx.x, nb);
-    const int c = lin / a.ntiles;
+    const int lin = xcd_logical(blockIdx.x, gridDim.x);
+    const int cs = lin / a.ntiles, seg = cs / a.L, c = cs - seg * a.L;
+    const XSeg sg = segs.s[seg];
     int I, J;
-    tile_ij(lin - c * a.ntiles, I, J);
+    tile_ij(lin - cs * a.ntiles, I, J);
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int64_t gstride = (int64_t)a.n_in * kRowBytes;
-    const uint8_t *base = a.chan + ((int64_t)c * a.NG + a.grp0) * gstride;
+    const uint8_t *base = a.chan + ((int64_t)c * a.NG + sg.grp0) * gstride;
     const uint8_t *pa = base + min(I * 32 + l32, a.n_in - 1) * kRowBytes + half * 16;
     const uint8_t *pb = base + min(J * 32 + l32, a.n_in - 1) * kRowBytes;
     const uint32_t sign = half ? 0u : 0x80000000u;
-    const int nstages = (a.ngrp + kFG - 1) / kFG;
+    const int nstages = (sg.ngrp + kFG - 1) / kFG;
 
     float4 fa[kFG], fb[kFG], fb2[kFG];
     auto fetch = [&](int s) {
 #pragma unroll
         for (int k = 0; k < kFG; ++k) {
             const int g = s * kFG + k;
-            const int64_t o = (int64_t)min(g, a.ngrp - 1) * gstride;
+            const int64_t o = (int64_t)min(g, sg.ngrp - 1) * gstride;
             fa[k] = *reinterpret_cast<const float4 *>(pa + o);
             fb[k] = *reinterpret_cast<const float4 *>(pb + o + half * 16);
             fb2[k] = *reinterpret_cast<const float4 *>(pb + o + (16 - half * 16));
-            if (g >= a.ngrp) fa[k] = make_float4(0.f, 0.f, 0.f, 0.f), fb[k] = fa[k], fb2[k] = fa[k];
+            if (g >= sg.ngrp) fa[k] = make_float4(0.f, 0.f, 0.f, 0.f), fb[k] = fa[k], fb2[k] = fa[k];
         }
     };
     v16f outr{}, outi{};
@@ -951,7 +951,7 @@ __global__ __launch_bounds__(64 * kFSWaves, 2) void xengine_f32_small(XArgs a) {
         __syncthreads();
     }
     if (wave != 0) return;
-    double2 *dst0 = reinterpret_cast<double2 *>(a.integ) + (int64_t)c * a.P;
+    double2 *dst0 = reinterpret_cast<double2 *>(sg.integ) + (int64_t)c * a.P;
     const int n2 = J * 32 + l32;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -959,7 +959,7 @@ __global__ __launch_bounds__(64 * kFSWaves, 2) void xengine_f32_small(XArgs a) {
         if (n1 < a.n_in && n2 <= n1) {
             double2 *dst = dst0 + (int64_t)n1 * (n1 + 1) / 2 + n2;
             double2 v = tot[r];
-            if (!a.first) {
+            if (!sg.first) {
                 const double2 old = *dst;
                 v.x += old.x;
                 v.y += old.y;
@@ -1050,22 +1050,25 @@ hipError_t launch_xengine(int xprec, const XArgs &args, hipStream_t s) {
         case MWAX_X_FP16:
             hipLaunchKernelGGL(xengine_mfma<MWAX_X_FP16>, dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
             break;
-        case MWAX_X_FP32: {
-            a.ntiles = xengine_tile_count(a.n_in, kFT);
-            const int64_t tiles = (int64_t)a.ntiles * a.L;
-            // fewer 64 x 64 tiles than the four per CU that are resident together
-            // would leave matrix cores idle; the small form has twice the waves per
-            // workgroup and up to four times the workgroups
-            if (tiles < 4 * device_cus()) {
-                a.ntiles = xengine_tile_count(a.n_in, 32);
-                hipLaunchKernelGGL(xengine_f32_small, dim3((unsigned)(a.ntiles * a.L)), dim3(64 * kFSWaves), 0, s, a);
-            } else {
-                hipLaunchKernelGGL(xengine_f32, dim3((unsigned)tiles), dim3(kThreads), 0, s, a);
-            }
-            break;
-        }
         default:
             return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_xengine_f32(const XArgs &args, const XSegList &segs, hipStream_t s) {
+    XArgs a = args;
+    if (segs.n < 1 || segs.n > kXSegs) return hipErrorInvalidValue;
+    a.ntiles = xengine_tile_count(a.n_in, kFT);
+    const int64_t tiles = (int64_t)a.ntiles * a.L * segs.n;
+    // fewer 64 x 64 tiles than the four per CU that are resident together
+    // would leave matrix cores idle; the small form has twice the waves per
+    // workgroup and up to four times the workgroups
+    if (tiles < 4 * device_cus()) {
+        a.ntiles = xengine_tile_count(a.n_in, 32);
+        hipLaunchKernelGGL(xengine_f32_small, dim3((unsigned)(a.ntiles * a.L * segs.n)), dim3(64 * kFSWaves), 0, s, a, segs);
+    } else {
+        hipLaunchKernelGGL(xengine_f32, dim3((unsigned)tiles), dim3(kThreads), 0, s, a, segs);
     }
     return hipGetLastError();
 }
@@ -1086,8 +1089,8 @@ hipError_t launch_xengine_batch(int xprec, const XBatchArgs &b, int grid, hipStr
 }
 
 hipError_t launch_xengine_avg(int xprec, const XAvgArgs &a, hipStream_t s) {
-    const int64_t blocks = (int64_t)a.N * a.ntiles;
-    if (blocks <= 0 || a.ngrp <= 0) return hipSuccess;
+    if (a.segs.n < 1 || a.segs.n > kXSegs) return hipErrorInvalidValue;
+    const int64_t blocks = (int64_t)a.N * a.ntiles * a.segs.n;
     switch (xprec) {
         case MWAX_X_INT8:
             hipLaunchKernelGGL(xengine_avg<MWAX_X_INT8>, dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
