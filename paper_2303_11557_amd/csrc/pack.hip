@@ -14,8 +14,12 @@
 // INT8 integrators hold Im V[n1,n2] - sum_m re_n1[m] (the X-engine forms its
 // imaginary operand from one's complements); the autos, whose imaginary parts
 // are zero, therefore hold -sum_m re_n1[m], and every entry of row n1 is
-// corrected exactly by subtracting its auto's imaginary part.  So INT8 slots are
-// cleared by a separate fill after the pack, never while it reads them.
+// corrected by subtracting its auto's imaginary part: exactly, in integers, or
+// for INT8 plans that average in their X-engine in FP64, where the same sums are
+// scaled and weighted over the channels.  Slots are cleared (where they have to
+// be) by a separate fill after the pack, never while it reads them.
+#include <algorithm>
+
 #include "mwax_internal.h"
 
 namespace mwax {
@@ -28,51 +32,72 @@ __device__ __forceinline__ int64_t tri_row(int64_t t) {
     return i;
 }
 
-// Exact INT8 sums of entry p = n1(n1+1)/2 + n2 of channel c (int32 or int64
-// integrators; int32 ones are within range, see kInt32MaxSpectra).
-__device__ __forceinline__ longlong2 int_vis(const PackArgs &a, int c, int64_t n1, int64_t p) {
-    const int64_t d = n1 * (n1 + 1) / 2 + n1;
-    if (a.i32) {
-        const int2 *integ = reinterpret_cast<const int2 *>(a.integ) + (int64_t)c * a.P;
-        const int2 v = integ[p];
-        return make_longlong2(v.x, (long long)v.y - integ[d].y);
-    }
-    const longlong2 *integ = reinterpret_cast<const longlong2 *>(a.integ) + (int64_t)c * a.P;
-    longlong2 v = integ[p];
-    v.y -= integ[d].y;
-    return v;
-}
+// What the integrators hold.
+enum Source { kI32, kI64, kF64, kF64Fix };   // kF64Fix: the row's auto is subtracted from the imaginary parts
+constexpr bool is_int(int S) { return S == kI32 || S == kI64; }
+constexpr bool needs_auto(int S) { return S != kF64; }
 
-__device__ __forceinline__ float2 scaled(const PackArgs &a, int64_t p, int64_t n1, int c) {
-    if (a.is_int) {
-        const longlong2 v = int_vis(a, c, n1, p);
+// Entry p of the channel whose integrators start at base (elements of the
+// source); d: the auto of p's row (sources that need it).
+template <int S>
+__device__ __forceinline__ auto entry(const void *base, int64_t p, int64_t d) {
+    if constexpr (S == kI32) {       // within range, see kInt32MaxSpectra
+        const int2 *v = reinterpret_cast<const int2 *>(base);
+        const int2 x = v[p];
+        return make_longlong2(x.x, (long long)x.y - v[d].y);
+    } else if constexpr (S == kI64) {
+        const longlong2 *v = reinterpret_cast<const longlong2 *>(base);
+        longlong2 x = v[p];
+        x.y -= v[d].y;
+        return x;
+    } else {
+        const double2 *v = reinterpret_cast<const double2 *>(base);
+        double2 x = v[p];
+        if constexpr (S == kF64Fix) x.y -= v[d].y;
+        return x;
+    }
+}
+template <int S>
+__device__ __forceinline__ const void *channel(const PackArgs &a, int c) {
+    return reinterpret_cast<const uint8_t *>(a.integ) + (int64_t)c * a.P * (S == kI32 ? 8 : 16);
+}
+// The scaled value in FP64: INT8 V_int s s (s = s_c), FP16 and FP32 V post.
+template <int S>
+__device__ __forceinline__ double2 scaled(const PackArgs &a, int c, int64_t p, int64_t d) {
+    const auto v = entry<S>(channel<S>(a, c), p, d);
+    if constexpr (is_int(S)) {
         const double s = (double)a.scales[c];
-        return make_float2((float)((double)v.x * s * s), (float)((double)v.y * s * s));
+        return make_double2((double)v.x * s * s, (double)v.y * s * s);
+    } else {
+        return make_double2(v.x * a.post, v.y * a.post);
     }
-    const double2 v = reinterpret_cast<const double2 *>(a.integ)[(int64_t)c * a.P + p];
-    return make_float2((float)(v.x * a.post), (float)(v.y * a.post));
 }
+__device__ __forceinline__ int64_t auto_of(int64_t n1) { return n1 * (n1 + 1) / 2 + n1; }
 
-__global__ void pack_tri_kernel(PackArgs a) {
-    const int64_t total = (int64_t)a.L * a.P;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-         t += (int64_t)gridDim.x * blockDim.x) {
-        const int c = (int)(t / a.P);
-        const int64_t p = t - (int64_t)c * a.P;
-        if (a.order == 2) {
-            reinterpret_cast<longlong2 *>(a.out)[t] = int_vis(a, c, tri_row(p), p);
-        } else if (a.is_int) {
-            reinterpret_cast<float2 *>(a.out)[t] = scaled(a, p, tri_row(p), c);
-        } else {
-            reinterpret_cast<float2 *>(a.out)[t] = scaled(a, p, 0, c);
-            if (a.clear) reinterpret_cast<double2 *>(a.integ)[t] = make_double2(0.0, 0.0);
+// A thread emits one pair over up to kPackCh channels: its row (a square root in
+// FP64) is found once, and the loads of four channels are in flight together.
+// Bound by HBM: the 2.98 GB of six uneven instances take 551 us (5.4 TB/s, part of
+// it from the last-level cache); one element per thread, with a 64-bit division to
+// find its channel, took 880 us.
+constexpr int kPackCh = 8;
+template <int S, bool RAW>
+__global__ __launch_bounds__(256) void pack_tri_kernel(PackArgs a, int per_thread) {
+    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int c0 = blockIdx.y * per_thread, c1 = min(a.L, c0 + per_thread);
+    if (p < a.P) {
+        const int64_t d = needs_auto(S) ? auto_of(tri_row(p)) : 0;
+#pragma unroll 4
+        for (int c = c0; c < c1; ++c) {
+            if constexpr (RAW) {
+                reinterpret_cast<longlong2 *>(a.out)[(int64_t)c * a.P + p] = entry<S>(channel<S>(a, c), p, d);
+            } else {
+                const double2 v = scaled<S>(a, c, p, d);
+                reinterpret_cast<float2 *>(a.out)[(int64_t)c * a.P + p] = make_float2((float)v.x, (float)v.y);
+            }
         }
     }
-    if (a.scales_out) {
-        for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < a.L;
-             c += (int64_t)gridDim.x * blockDim.x)
-            a.scales_out[c] = a.scales[c];
-    }
+    if (a.scales_out && blockIdx.x == 0 && c0 + (int)threadIdx.x < c1)
+        a.scales_out[c0 + threadIdx.x] = a.scales[c0 + threadIdx.x];
 }
 
 // Emission with channel averaging in the same pass (Sec. 2.6): output channel o
@@ -82,66 +107,90 @@ __global__ void pack_tri_kernel(PackArgs a) {
 // optionally divided by the pair's occupancy weight; FP64 sums, one rounding.
 // Reading the integrators once replaces a pack to 6,400-channel visibilities
 // and a second pass over them.
-__global__ void pack_avg_kernel(PackArgs a) {
-    const int N = a.L / a.F, oc = N / 2, half = a.F / 2;
-    const bool even = (a.F & 1) == 0;
-    const int64_t total = (int64_t)N * a.P;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-         t += (int64_t)gridDim.x * blockDim.x) {
-        const int o = (int)(t / a.P);
-        const int64_t p = t - (int64_t)o * a.P;
-        const int64_t n1 = a.is_int ? tri_row(p) : 0;
-        const bool centre = a.F > 1 && o == oc;
-        double re = 0.0, im = 0.0, wsum = 0.0;
-        for (int d = -half; d <= half; ++d) {
-            if (centre && d == 0) continue;
-            const double w = even && (d == -half || d == half) ? 0.5 : 1.0;
-            const int c = ((a.L / 2 + (o - oc) * a.F + d) % a.L + a.L) % a.L;
-            double vr, vi;
-            if (a.is_int) {
-                const longlong2 v = int_vis(a, c, n1, p);
-                const double sc = (double)a.scales[c];
-                vr = (double)v.x * sc * sc;
-                vi = (double)v.y * sc * sc;
-            } else {
-                const double2 v = reinterpret_cast<const double2 *>(a.integ)[(int64_t)c * a.P + p];
-                vr = v.x * a.post;
-                vi = v.y * a.post;
-            }
-            re += w * vr;
-            im += w * vi;
-            wsum += w;
-        }
-        double div = wsum;
-        if (a.avg_w) {
-            const double wp = (double)a.avg_w[p];
-            if (wp > 0.0) div *= wp;
-        }
-        reinterpret_cast<float2 *>(a.out)[t] = make_float2((float)(re / div), (float)(im / div));
+template <int S>
+__global__ __launch_bounds__(256) void pack_avg_kernel(PackArgs a) {
+    const int N = a.L / a.F, oc = N / 2, half = a.F / 2, o = blockIdx.y;
+    const bool even = (a.F & 1) == 0, centre = a.F > 1 && o == oc;
+    const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (p >= a.P) return;
+    const int64_t d = needs_auto(S) ? auto_of(tri_row(p)) : 0;
+    double re = 0.0, im = 0.0, wsum = 0.0;
+    int c = ((a.L / 2 + (o - oc) * a.F - half) % a.L + a.L) % a.L;
+    auto add = [&](double w) {
+        const double2 v = scaled<S>(a, c, p, d);
+        re += w * v.x;
+        im += w * v.y;
+        wsum += w;
+        c = c + 1 == a.L ? 0 : c + 1;
+    };
+    auto run = [&](int n) {
+#pragma unroll 4
+        for (int k = 0; k < n; ++k) add(1.0);
+    };
+    const double we = even ? 0.5 : 1.0;   // the outermost two
+    if (a.F == 1) {
+        add(1.0);
+    } else {
+        add(we);
+        run(half - 1);
+        if (centre) c = c + 1 == a.L ? 0 : c + 1;
+        else add(1.0);
+        run(half - 1);
+        add(we);
     }
+    double div = wsum;
+    if (a.avg_w) {
+        const double wp = (double)a.avg_w[p];
+        if (wp > 0.0) div *= wp;
+    }
+    reinterpret_cast<float2 *>(a.out)[(int64_t)o * a.P + p] = make_float2((float)(re / div), (float)(im / div));
 }
 
-// gather pass of the tile-baseline order (integrators cleared afterwards)
-__global__ void pack_tilebl_kernel(PackArgs a) {
-    const int64_t nt = a.n_in / 2;
-    const int64_t total = nt * (nt + 1) / 2 * a.L * 4;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-         t += (int64_t)gridDim.x * blockDim.x) {
-        const int pp = (int)(t & 3);
-        const int64_t rest = t >> 2;
-        const int c = (int)(rest % a.L);
-        const int64_t bl = rest / a.L;
-        const int64_t ta = tri_row(bl);
-        const int64_t tb = bl - ta * (ta + 1) / 2;
-        const int64_t r = 2 * ta + (pp >> 1), s = 2 * tb + (pp & 1);
-        float2 v;
-        if (r >= s) {
-            v = scaled(a, r * (r + 1) / 2 + s, r, c);
-        } else {
-            v = scaled(a, s * (s + 1) / 2 + r, s, c);
-            v.y = -v.y;
+// Tile-baseline order: a workgroup moves kBlB baselines of one tile row (tile a,
+// consecutive tiles b) x kBlC channels through LDS.  The products of a baseline row
+// are two rows of the triangle (the inputs of tile a), contiguous over the inputs
+// of the tiles b, so reads run along the inputs and writes along the channels.
+constexpr int kBlB = 16, kBlC = 16;
+template <int S>
+__global__ __launch_bounds__(256) void pack_tilebl_kernel(PackArgs a) {
+    __shared__ float2 img[kBlB][kBlC][5];    // [baseline][channel][product], padded
+    // workgroup -> (tile row ta, run of kBlB tiles tb): rows hold 1, .., ceil(nt / kBlB) runs
+    int run = blockIdx.x, ta = 0;
+    {
+        // rows kBlB k .. kBlB k + kBlB - 1 hold k + 1 runs each
+        int k = 0;
+        while (run >= kBlB * (k + 1)) {
+            run -= kBlB * (k + 1);
+            ++k;
         }
-        reinterpret_cast<float2 *>(a.out)[t] = v;
+        ta = kBlB * k + run / (k + 1);
+        run %= k + 1;
+    }
+    const int nt = a.n_in / 2;
+    if (ta >= nt) return;
+    const int tb0 = run * kBlB, nb = min(kBlB, ta + 1 - tb0);
+    const int c0 = blockIdx.y * kBlC, nc = min(kBlC, a.L - c0);
+    // lanes along the 2 kBlB inputs of the tiles b; 8 (channel, input of tile a) at a time
+    const int s = threadIdx.x % (2 * kBlB), k0 = threadIdx.x / (2 * kBlB);
+    for (int k = k0; k < 2 * nc; k += 256 / (2 * kBlB)) {
+        const int c = c0 + (k >> 1), p1 = k & 1;
+        const int r = 2 * ta + p1, n2 = 2 * tb0 + s;
+        if (s < 2 * nb) {
+            double2 v;
+            if (n2 <= r) {
+                v = scaled<S>(a, c, (int64_t)r * (r + 1) / 2 + n2, auto_of(r));
+            } else {   // auto-tile XY: the conjugate of the mirrored entry
+                v = scaled<S>(a, c, (int64_t)n2 * (n2 + 1) / 2 + r, auto_of(n2));
+                v.y = -v.y;
+            }
+            img[s >> 1][k >> 1][2 * p1 + (s & 1)] = make_float2((float)v.x, (float)v.y);
+        }
+    }
+    __syncthreads();
+    const int64_t bl0 = (int64_t)ta * (ta + 1) / 2 + tb0;
+    for (int u = threadIdx.x; u < nb * nc * 4; u += 256) {
+        const int b = u / (nc * 4), rest = u - b * nc * 4;
+        reinterpret_cast<float2 *>(a.out)[((bl0 + b) * a.L + c0) * 4 + rest] = img[b][rest >> 2][rest & 3];
     }
 }
 
@@ -174,26 +223,35 @@ static size_t clear_bytes(const PackArgs &a) {
     return ((size_t)a.L * a.P * (a.i32 ? 8 : 16) + 15) / 16 * 16;
 }
 
-hipError_t launch_pack(const PackArgs &a, hipStream_t s) {
+template <int S>
+static hipError_t launch_pack_source(const PackArgs &a, hipStream_t s) {
+    const unsigned gx = (unsigned)((a.P + 255) / 256);
     if (a.order == 3) {
         if (a.F < 1 || a.L % a.F != 0) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(pack_avg_kernel, dim3(grid_for((int64_t)(a.L / a.F) * a.P)), dim3(256), 0, s, a);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess || !a.clear) return e;
-        return a.is_int ? launch_fill_zero(a.integ, clear_bytes(a), s)
-                        : launch_fill_zero(a.integ, (size_t)a.L * a.P * 16, s);
+        hipLaunchKernelGGL(pack_avg_kernel<S>, dim3(gx, (unsigned)(a.L / a.F)), dim3(256), 0, s, a);
+    } else if (a.order == MWAX_ORDER_TILE_BL) {
+        const int k = (a.n_in / 2 + kBlB - 1) / kBlB;   // tile rows in units of kBlB
+        hipLaunchKernelGGL(pack_tilebl_kernel<S>, dim3((unsigned)(kBlB * k * (k + 1) / 2), (unsigned)((a.L + kBlC - 1) / kBlC)),
+                           dim3(256), 0, s, a);
+    } else {
+        // small outputs: fewer channels per thread, at least eight workgroups per CU
+        // (4 tiles: 2.8 us with one channel per thread, 5.0 with eight)
+        const int per = (int)std::max<int64_t>(1, std::min<int64_t>(kPackCh, (int64_t)gx * a.L / 2048));
+        const dim3 grid(gx, (unsigned)((a.L + per - 1) / per));
+        if (a.order != 2) {
+            hipLaunchKernelGGL((pack_tri_kernel<S, false>), grid, dim3(256), 0, s, a, per);
+        } else {
+            if constexpr (!is_int(S)) return hipErrorInvalidValue;
+            else hipLaunchKernelGGL((pack_tri_kernel<S, true>), grid, dim3(256), 0, s, a, per);
+        }
     }
-    if (a.order == MWAX_ORDER_TILE_BL) {
-        const int64_t nt = a.n_in / 2;
-        const int64_t total = nt * (nt + 1) / 2 * a.L * 4;
-        hipLaunchKernelGGL(pack_tilebl_kernel, dim3(grid_for(total)), dim3(256), 0, s, a);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess || !a.clear) return e;
-        return launch_fill_zero(a.integ, clear_bytes(a), s);
-    }
-    hipLaunchKernelGGL(pack_tri_kernel, dim3(grid_for((int64_t)a.L * a.P)), dim3(256), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !a.clear || !a.is_int) return e;
+    return hipGetLastError();
+}
+
+hipError_t launch_pack(const PackArgs &a, hipStream_t s) {
+    hipError_t e = a.is_int ? (a.i32 ? launch_pack_source<kI32>(a, s) : launch_pack_source<kI64>(a, s))
+                            : (a.fix_im ? launch_pack_source<kF64Fix>(a, s) : launch_pack_source<kF64>(a, s));
+    if (e != hipSuccess || !a.clear) return e;
     return launch_fill_zero(a.integ, clear_bytes(a), s);
 }
 
