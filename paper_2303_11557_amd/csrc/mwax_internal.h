@@ -255,7 +255,7 @@ struct XAvgArgs {
     int32_t L;
     int32_t F;              // fine channels per output channel
     int32_t N;              // output channels, L / F
-    int32_t ntiles;         // 64-edge lower-triangle tiles per channel
+    int32_t ntiles;         // workgroups per output channel (set by launch_xengine_avg)
     int64_t P;
     XSegList segs;          // integrators: [N][P] (double2)
 };

@@ -659,7 +659,6 @@ mwax_status mwax_correlate(mwax_plan p) {
                 v.L = p->L;
                 v.F = p->favg;
                 v.N = p->L / p->favg;
-                v.ntiles = xengine_tile_count(p->n_in, kXTileSmall);
                 v.P = p->P;
                 v.segs = q;
                 return launch_xengine_avg(p->xprec, v, p->stream);
@@ -708,7 +707,7 @@ static mwax_status emit(mwax_plan p, void *d_vis, float *d_scales, int32_t max_i
         a.scales_out = d_scales ? d_scales + (size_t)n * p->L : nullptr;
         a.order = order;
         a.clear = p->clear_on_emit && !pre;
-        a.fix_im = 0;
+        a.fix_im = pre && p->xprec == MWAX_X_INT8;
         a.i32 = p->integ32;
         a.L = pre ? p->L / p->favg : p->L;
         a.n_in = p->n_in;

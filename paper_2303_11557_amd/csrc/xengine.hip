@@ -510,6 +510,45 @@ __global__ __launch_bounds__(kThreads, 2) void xengine_batch(XBatchArgs b) {
     }
 }
 
+// Lower triangle in 32 x 32 blocks, four to a workgroup (one per wave), for the
+// kernels on 64-edge tiles (nt of them along an edge).  Workgroup t of a channel:
+//   t < nt (nt - 1) / 2: the four blocks of an off-diagonal tile;
+//   then, for every four diagonal tiles (three blocks each), three workgroups: the
+//   blocks of one tile and one block of the group's last tile;
+//   then the diagonal tiles left (nt mod 4), three blocks and an idle wave each.
+// An idle wave does not only leave its SIMD empty: the other SIMDs, which have
+// more to do, hold back the waves it would run instead.
+// Four LDS slots hold 32 rows each; wave w copies slot w.
+struct TriBlock {
+    int ra, rb;          // row blocks of the wave's rows and columns (ra >= rb), or ra < 0: idle
+    int sa, sb;          // the slots that hold them
+    int copy;            // row block this wave copies into its slot
+};
+__host__ __device__ inline int tri_groups(int nt) { return nt * (nt - 1) / 2 + 3 * (nt / 4) + nt % 4; }
+__device__ __forceinline__ TriBlock tri_block(int nt, int t, int role, int wave) {
+    const int noff = nt * (nt - 1) / 2;
+    TriBlock b;
+    if (t < noff) {
+        int I, J;
+        tile_ij(t, I, J);
+        ++I;
+        b.ra = 2 * I + (role >> 1), b.rb = 2 * J + (role & 1);
+        b.sa = role >> 1, b.sb = 2 + (role & 1);
+        b.copy = wave < 2 ? 2 * I + wave : 2 * J + (wave & 1);
+        return b;
+    }
+    const int u = t - noff, g = nt / 4, j = u % 3;
+    const bool group = u < 3 * g;
+    const int d = group ? u / 3 * 4 + j : 4 * g + (u - 3 * g), e = group ? u / 3 * 4 + 3 : d;
+    // blocks of a diagonal tile: 0 (0, 0), 1 (1, 0), 2 (1, 1)
+    const int k = role < 3 ? role : j, x = role < 3 ? d : e, s0 = role < 3 ? 0 : 2;
+    b.ra = 2 * x + (k > 0), b.rb = 2 * x + (k > 1);
+    b.sa = s0 + (k > 0), b.sb = s0 + (k > 1);
+    if (role == 3 && !group) b.ra = -1;
+    b.copy = 2 * (wave < 2 ? d : e) + (wave & 1);
+    return b;
+}
+
 // ---------------------------------------------------------------------------
 // Averaging X-engine (Sec. 2.6 applied inside the correlation): one workgroup =
 // one output channel o of N = L / F x one 64 x 64 tile.  It correlates the fine
@@ -523,9 +562,15 @@ __global__ __launch_bounds__(kThreads, 2) void xengine_batch(XBatchArgs b) {
 // integration, stored) once into FP64 integrators [N][P].  The fine-channel
 // integrators are never written: per 250 ms integration at 256 tiles and
 // L = 6400 that is 6.7 GB of flushes and 6.7 GB of pack reads avoided.
-// The INT8 Im operand is the exact negation (-im, re), not the one's
-// complement of the per-channel kernel, so each channel's partials are its
-// exact sums before scaling.
+// The INT8 Im operand is the one's complement of the per-channel kernel: each
+// channel's imaginary partials lack sum_m re_n1[m], and so, scaled and weighted
+// alike, do the sums; the pack step subtracts the autos' sums, which hold just
+// that.  Bound by the copies from L2 into LDS: 512 inputs at 40 kHz read every row
+// nine times, 15 GB per four 250 ms integrations, 12 TB/s at 1.25 ms (the copies
+// of the per-channel kernel reach no more alone); the VALU's conversion and
+// weighted addition of every partial comes next.  1.42 ms with the exact negation,
+// cleared partials and an idle wave on every diagonal tile; 1.74 ms with a launch
+// per integration.
 // ---------------------------------------------------------------------------
 // Copies run three stages ahead here (two in the per-channel kernel): a work
 // item's stages are short (4 MFMAs per wave at 250 ms integrations) and every
@@ -548,14 +593,11 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
     const int lin = xcd_logical(blockIdx.x, gridDim.x);
     const int os = lin / a.ntiles, seg = os / a.N, o = os - seg * a.N;
     const XSeg sg = a.segs.s[seg];
-    int I, J;
-    tile_ij(lin - os * a.ntiles, I, J);
-    const int rowA0 = I * TE, rowB0 = J * TE;
     const int lane = threadIdx.x & 63;
     const int half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int wr = wave >> 1, wc = wave & 1;
-    const bool active = !((I == J && wr < wc) || rowA0 + wr * 32 >= a.n_in || rowB0 + wc * 32 >= a.n_in);
+    const TriBlock tb = tri_block((a.n_in + TE - 1) / TE, lin - os * a.ntiles, (wave + lin) & 3, wave);
+    const bool active = tb.ra >= 0 && tb.ra * 32 < a.n_in;
 
     // the fine channels of o: offsets d = -h .. h (DC skipped in the centre one),
     // channel (L/2 + (o - N/2) F + d) mod L.  They are walked with cursors: no
@@ -572,15 +614,12 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
         return n >= a.L ? n - a.L : n;
     };
 
-    // copies: waves 0, 1 move 32 rows each of the A panel, waves 2, 3 of the B panel
-    const int cblk = wave & 1, cpanel = (wave >> 1) * kPanel;
-    const int chalf = lane >> 5, crow = cblk * 32 + (lane & 31);
-    const int rowC0 = wave < 2 ? rowA0 : rowB0;
-    const uint32_t offR = (uint32_t)min(rowC0 + crow, a.n_in - 1) * kRowBytes + chalf * 16;
-    const uint32_t offZ = (uint32_t)crow * kRowBytes + chalf * 16;
+    // copies: wave w moves the 32 rows of slot w
+    const uint32_t offR = (uint32_t)min(tb.copy * 32 + l32, a.n_in - 1) * kRowBytes + half * 16;
+    const uint32_t offZ = (uint32_t)l32 * kRowBytes + half * 16;
     const int64_t gstride = (int64_t)a.n_in * kRowBytes;
     const int64_t cstride = a.NG * gstride;       // bytes between channels
-    const int ldst = cpanel + cblk * kBlock;
+    const int ldst = (wave >> 1) * kPanel + (wave & 1) * kBlock;
     const int spc = (sg.ngrp + kXG - 1) / kXG;     // stages per channel
     const int nst = nch * spc;
 
@@ -596,6 +635,8 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
 #pragma unroll
         for (int k = 0; k < kXG; ++k) {
             const bool in = live && cp_g + k < sg.ngrp;
+            // (selected as a whole: with a selected base the compiler puts the copies
+            // behind a branch and waits for all of them at every stage)
             const uint8_t *src = in ? cp_src + k * gstride + offR : kZeroGroup + offZ;
             __builtin_amdgcn_global_load_lds(src, buf + k * kGroupPitch + ldst, 16, 0, 0);
         }
@@ -616,10 +657,13 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
     float sr[16], si[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) sr[r] = si[r] = 0.0f;
-    const int fa_off = wr * kBlock + half * 512 + l32 * 16;
-    const int fb_off = kPanel + wc * kBlock + half * 512 + l32 * 16;
+    const int fa_off = (tb.sa >> 1) * kPanel + (tb.sa & 1) * kBlock + half * 512 + l32 * 16;
+    const int fb_off = (tb.sb >> 1) * kPanel + (tb.sb & 1) * kBlock + half * 512 + l32 * 16;
+    constexpr uint32_t kFlip = INT8 ? 0xffffffffu : 0x80008000u;
 
-    auto compute = [&](const uint8_t *st) {
+    // FIRST: the channel's first stage starts its partial sums (no cleared registers)
+    auto compute = [&](const uint8_t *st, auto first_c) {
+        constexpr bool FIRST = decltype(first_c)::value;
         uint4 fa[2], fb[2];
         fa[0] = *reinterpret_cast<const uint4 *>(st + fa_off);
         fb[0] = *reinterpret_cast<const uint4 *>(st + fb_off);
@@ -630,11 +674,9 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
                 fb[(k + 1) & 1] = *reinterpret_cast<const uint4 *>(st + (k + 1) * kGroupPitch + fb_off);
             }
             const uint4 v = fb[k & 1];
-            uint4 fb2;
-            if constexpr (INT8) fb2 = make_uint4(neg_i8x4(v.z), neg_i8x4(v.w), v.x, v.y);
-            else fb2 = make_uint4(v.z ^ 0x80008000u, v.w ^ 0x80008000u, v.x, v.y);
-            re = T::mma(fa[k & 1], v, re);
-            im = T::mma(fa[k & 1], fb2, im);
+            const uint4 fb2 = make_uint4(v.z ^ kFlip, v.w ^ kFlip, v.x, v.y);
+            re = T::mma(fa[k & 1], v, FIRST && k == 0 ? acc_t{} : re);
+            im = T::mma(fa[k & 1], fb2, FIRST && k == 0 ? acc_t{} : im);
         }
     };
     // Weight of every channel index ci (weight / weight total, times s_c^2): a
@@ -664,7 +706,10 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
         constexpr int B = decltype(b_c)::value;
         copy_next(bufs[(B + kAvgDist) % kNBuf]);
         if (s < nst) {
-            if (active) compute(bufs[B]);
+            if (active) {
+                if (cm_ls == 0) compute(bufs[B], std::true_type{});
+                else compute(bufs[B], std::false_type{});
+            }
             if (++cm_ls == spc) {
                 // the channel's partials, scaled and weighted, into the sums
                 if (active) {
@@ -676,8 +721,6 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
                         sr[r] = fmaf(coef, (float)re[r], sr[r]);
                         si[r] = fmaf(coef, (float)im[r], si[r]);
                     }
-                    re = acc_t{};
-                    im = acc_t{};
                 }
                 cm_ls = 0;
                 if ((++cm_ci & 255) == 0 && cm_ci < nch) load_window(cm_ci);
@@ -699,10 +742,10 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
 
     if (active) {
         double2 *dst0 = reinterpret_cast<double2 *>(sg.integ) + (int64_t)o * a.P;
-        const int n2 = rowB0 + wc * 32 + l32;
+        const int n2 = tb.rb * 32 + l32;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int n1 = rowA0 + wr * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+            const int n1 = tb.ra * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
             if (n1 < a.n_in && n2 <= n1) {
                 double2 *dst = dst0 + (int64_t)n1 * (n1 + 1) / 2 + n2;
                 double2 v = make_double2((double)sr[r], (double)si[r]);
@@ -773,25 +816,20 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_f32(XArgs a, XSegList seg
     const int lin = xcd_logical(blockIdx.x, gridDim.x);
     const int cs = lin / a.ntiles, seg = cs / a.L, c = cs - seg * a.L;
     const XSeg sg = segs.s[seg];
-    int I, J;
-    tile_ij(lin - cs * a.ntiles, I, J);
-    const int rowA0 = I * kFT, rowB0 = J * kFT;
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    // the wave of each block turns with the tile: a diagonal tile's idle wave (and
-    // its SIMD) is another one from workgroup to workgroup
-    const int role = (wave + lin) & 3, wr = role >> 1, wc = role & 1;
-    const bool active = !((I == J && wr < wc) || rowA0 + wr * 32 >= a.n_in || rowB0 + wc * 32 >= a.n_in);
+    // the wave of each block turns with the workgroup: an idle one is on another
+    // SIMD from workgroup to workgroup
+    const TriBlock tb = tri_block((a.n_in + kFT - 1) / kFT, lin - cs * a.ntiles, (wave + lin) & 3, wave);
+    const bool active = tb.ra >= 0 && tb.ra * 32 < a.n_in;
 
-    // copies: waves 0, 1 move 32 rows each of the A panel, waves 2, 3 of the B
-    // panel.  Rows past the last input are read from a clamped address: they reach
-    // only outputs that are never flushed.
-    const int cblk = wave & 1, crow = cblk * 32 + l32;
-    const uint32_t offR = (uint32_t)min((wave < 2 ? rowA0 : rowB0) + crow, a.n_in - 1) * kRowBytes + half * 16;
-    const uint32_t offZ = (uint32_t)crow * kRowBytes + half * 16;
+    // copies: wave w moves the 32 rows of slot w.  Rows past the last input are read
+    // from a clamped address: they reach only outputs that are never flushed.
+    const uint32_t offR = (uint32_t)min(tb.copy * 32 + l32, a.n_in - 1) * kRowBytes + half * 16;
+    const uint32_t offZ = (uint32_t)l32 * kRowBytes + half * 16;
     const int64_t gstride = (int64_t)a.n_in * kRowBytes;
     const uint8_t *base = a.chan + ((int64_t)c * a.NG + sg.grp0) * gstride;
-    const int ldst = (wave >> 1) * kFPanel + cblk * kBlock;
+    const int ldst = (wave >> 1) * kFPanel + (wave & 1) * kBlock;
     const int nstages = (sg.ngrp + kFG - 1) / kFG;
     auto copy_stage = [&](int s, uint8_t *buf) {
 #pragma unroll
@@ -802,8 +840,8 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_f32(XArgs a, XSegList seg
         }
     };
 
-    const int fa_off = wr * kBlock + half * 512 + l32 * 16;
-    const int fb_off = kFPanel + wc * kBlock + half * 512 + l32 * 16;
+    const int fa_off = (tb.sa >> 1) * kFPanel + (tb.sa & 1) * kBlock + half * 512 + l32 * 16;
+    const int fb_off = (tb.sb >> 1) * kFPanel + (tb.sb & 1) * kBlock + half * 512 + l32 * 16;
     const int fb2_off = fb_off + (half ? -512 : 512);
     const uint32_t sign = half ? 0u : 0x80000000u;
     v16f outr{}, outi{};
@@ -823,7 +861,7 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_f32(XArgs a, XSegList seg
     auto flush = [&]() {
         // opaque, so that the 16 addresses are not formed ahead of the K loop and
         // held in registers through it
-        int fr0 = rowA0 + wr * 32, fc0 = rowB0 + wc * 32;
+        int fr0 = __builtin_amdgcn_readfirstlane(tb.ra * 32), fc0 = __builtin_amdgcn_readfirstlane(tb.rb * 32);
         asm volatile("" : "+s"(fr0), "+s"(fc0));
         double2 *dst0 = reinterpret_cast<double2 *>(sg.integ) + (int64_t)c * a.P;
         const int n2 = fc0 + l32;
@@ -1059,7 +1097,7 @@ hipError_t launch_xengine(int xprec, const XArgs &args, hipStream_t s) {
 hipError_t launch_xengine_f32(const XArgs &args, const XSegList &segs, hipStream_t s) {
     XArgs a = args;
     if (segs.n < 1 || segs.n > kXSegs) return hipErrorInvalidValue;
-    a.ntiles = xengine_tile_count(a.n_in, kFT);
+    a.ntiles = tri_groups((a.n_in + kFT - 1) / kFT);
     const int64_t tiles = (int64_t)a.ntiles * a.L * segs.n;
     // fewer 64 x 64 tiles than the four per CU that are resident together
     // would leave matrix cores idle; the small form has twice the waves per
@@ -1088,7 +1126,9 @@ hipError_t launch_xengine_batch(int xprec, const XBatchArgs &b, int grid, hipStr
     return hipGetLastError();
 }
 
-hipError_t launch_xengine_avg(int xprec, const XAvgArgs &a, hipStream_t s) {
+hipError_t launch_xengine_avg(int xprec, const XAvgArgs &args, hipStream_t s) {
+    XAvgArgs a = args;
+    a.ntiles = tri_groups((a.n_in + kTileSmall - 1) / kTileSmall);
     if (a.segs.n < 1 || a.segs.n > kXSegs) return hipErrorInvalidValue;
     const int64_t blocks = (int64_t)a.N * a.ntiles * a.segs.n;
     switch (xprec) {
