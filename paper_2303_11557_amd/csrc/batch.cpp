@@ -404,7 +404,12 @@ std::vector<int32_t> block_ranges(const std::vector<int64_t> &work, int grid) {
         // whole rounds of the 8 XCDs: the F-engine then hands each XCD one
         // contiguous range of items per round, so the output lines that adjacent
         // items share are completed in one L2
-        if (nb >= 8) nb &= ~(int64_t)7;
+        if (nb >= 8) {
+            nb &= ~(int64_t)7;
+            // and no partly filled last round: as many rounds with fewer workgroups
+            const int64_t rounds = ceil_div(work[d], nb);
+            nb = std::min(nb, ceil_div(ceil_div(work[d], rounds), 8) * 8);
+        }
         b0[d + 1] = (int32_t)(b0[d] + nb);
     }
     return b0;

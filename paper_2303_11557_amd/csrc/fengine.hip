@@ -154,11 +154,10 @@ struct FCfg {
     // extra registers keep the occupancy)
     static constexpr bool PREFETCH = XP != MWAX_X_FP32 && L2 > 1 && (L <= 256 || XP == MWAX_X_INT8) && !DIRECT;
     static_assert(R >= 1 && NGWG * PPG == PACKS * R && (PPG == 1 || GPW == 1), "bad decomposition");
-    // workgroups of a single-plan launch (each takes items in rounds): enough that
-    // the workgroups holding adjacent items stay in step (their rows share output
-    // lines), few enough that each one's set-up is spread over tens of items.
-    // Measured at 256 tiles, 8 s: 65,536 at every length but 256, where 131,072
-    // is 10 % faster (32,768 - 262,144 swept).
+    // most workgroups of a single-plan launch (main_grid): each takes items in
+    // rounds, and in too many rounds the workgroups holding adjacent items (their rows
+    // share output lines) drift apart.  Measured at 256 tiles, 8 s: 65,536 at every
+    // length but 256, where 131,072 is 10 % faster (32,768 - 262,144 swept).
     static constexpr int64_t GRID_CAP = L == 256 ? 131072 : 65536;
 };
 
@@ -728,6 +727,20 @@ constexpr int cfg_value_lds(bool stats) {
                  : C::OUT_BYTES + C::STAGE_BYTES + C::EX_BYTES;
 }
 
+// Workgroups of a single-plan launch over `items` items: whole rounds (a last round
+// of a few items costs as much as a full one), about eight of them, so that each
+// workgroup's set-up (twiddles, scales) is spread over several items, with no fewer
+// than 2,048 workgroups (all that can be resident) and no more than cap.  Rounds of
+// the 8 XCDs.  256 tiles, 1 s INT8 at L = 128 / 256: 881, 983 -> 720, 809 us with
+// 65,536 workgroups (2.4 rounds) before; 64 tiles: 242 -> 175; 128 tiles at L = 512
+// / 1024: 564, 580 -> 482, 502; 256 tiles, 8 s: 19.5 -> 20 rounds, 5.59 -> 5.41 ms.
+int main_grid(int64_t items, int64_t cap) {
+    constexpr int64_t kRounds = 8, kLeast = 2048;
+    if (items <= kLeast) return (int)items;
+    const int64_t rounds = std::max((items + cap - 1) / cap, std::min(kRounds, (items + kLeast - 1) / kLeast));
+    return (int)(((items + rounds - 1) / rounds + 7) / 8 * 8);
+}
+
 template <int L, int XP>
 hipError_t launch_L(const FArgs &a, hipStream_t s) {
     using C = FCfg<L, XP>;
@@ -735,7 +748,7 @@ hipError_t launch_L(const FArgs &a, hipStream_t s) {
     if (a.R != C::R) return hipErrorInvalidValue;
     const int lds = fengine_lds_bytes(L, XP, a.R, stats);
     int grid = fengine_grid(a.n_in, a.R, a.ngrp, stats);
-    if (!stats) grid = (int)std::min<int64_t>((int64_t)a.ngrp * ((a.n_in + C::R - 1) / C::R), C::GRID_CAP);
+    if (!stats) grid = main_grid((int64_t)a.ngrp * ((a.n_in + C::R - 1) / C::R), C::GRID_CAP);
     if (grid < 1) return hipSuccess;
     // allow dynamic LDS beyond the default limit (once per instantiation)
     const int variant = stats ? 1 : (a.dl ? 2 : 0);
