@@ -108,3 +108,18 @@ def test_fscrunch_zero_integrations():
     out = mwax.fscrunch(vis, 4)
     torch.cuda.synchronize()
     assert out.shape == (0, 4, 3)
+
+
+@pytest.mark.parametrize("n_in,L,F,n_ints", [
+    (2, 8, 2, 1),           # odd pair count: the last pair alone
+    (129, 512, 2, 1),       # odd pair count, runs of four output channels, even F
+    (129, 600, 5, 2),       # as before, odd F, a ragged last run
+    (129, 512, 512, 1),     # one output channel over the whole band, wrapping
+])
+def test_fscrunch_pairs_of_pairs_bit_exact(n_in, L, F, n_ints):
+    P = n_in * (n_in + 1) // 2
+    r = np.random.default_rng(n_in + L + F)
+    vis = (r.standard_normal((n_ints, L, P)) + 1j * r.standard_normal((n_ints, L, P))).astype(np.complex64)
+    g = mwax.fscrunch(torch.from_numpy(vis).cuda(), F).cpu().numpy()
+    re, im = expected(vis, F)
+    assert np.array_equal(g.real, re) and np.array_equal(g.imag, im)
