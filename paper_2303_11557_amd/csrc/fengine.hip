@@ -145,8 +145,8 @@ struct FCfg {
     static constexpr int OUT_BYTES = L * CP;
     static constexpr int STAGE_BYTES = L2 > 1 && !DIRECT ? (ALIAS ? THREADS / 64 * WAVE_PITCH : R * G * SP) : 0;
     static constexpr int EX_BYTES = L2 > 1 && !ALIAS ? THREADS / 64 * WAVE_EX : 0;
-    // statistics pass: per-lane channel sums (L1 floats) and populated-frame counts
-    static constexpr int RED_BYTES = THREADS * (L1 + 1) * 4;
+    // statistics pass: per-lane channel sums (L1 floats) and the populated-frame count
+    static constexpr int RED_BYTES = THREADS * L1 * 4 + 16;
     // waves per SIMD the registers are held to (0: the compiler's choice); four
     // would spill 7 to 15 registers and is slower (L = 256: 482 us)
     static constexpr int MINW = SPLIT ? 3 : 0;
@@ -679,8 +679,9 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
         int *redp = reinterpret_cast<int *>(red + C::THREADS * L1);
 #pragma unroll
         for (int i = 0; i < L1; ++i) red[(gg * L2 + r) * L1 + i] = acc[i];
-        redp[tid] = popc;
+        if (tid == 0) *redp = 0;
         __syncthreads();
+        if (popc) atomicAdd(redp, popc);
         constexpr int NSLOT = C::THREADS / L2;
         // partial row of this workgroup: L channel sums, then the populated count
         double *row = a.stats + (int64_t)wg * (L + 1);
@@ -690,11 +691,8 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
             for (int sl = 0; sl < NSLOT; ++sl) sum += (double)red[(sl * L2 + rr) * L1 + i];
             row[chan_of<L, XP>(rr, i)] = sum;
         }
-        if (tid == 0) {
-            int64_t n = 0;
-            for (int t = 0; t < C::THREADS; ++t) n += redp[t];
-            row[L] = (double)n;
-        }
+        __syncthreads();
+        if (tid == 0) row[L] = (double)*redp;
     }
 }
 
