@@ -166,8 +166,13 @@ int64_t eff_chunk(mwax_batch b, int i) {
 
 int nblk_of(mwax_plan p) { return (p->n_in + p->R - 1) / p->R; }
 
-// X-engine tiles per channel of instance i at its tile edge.
-int ntiles_of(mwax_batch b, int i) { return xengine_tile_count(b->inst[i]->n_in, b->tile[i]); }
+// X-engine tile edge of instance i: the chosen one, or that of a small FP16 plan,
+// whose order of summation is not a matter of choice.
+int edge_of(mwax_batch b, int i) {
+    return b->xprec == MWAX_X_FP16 && b->inst[i]->n_in <= kXSmallInputs ? kXTileTiny : b->tile[i];
+}
+// X-engine tiles per channel of instance i.
+int ntiles_of(mwax_batch b, int i) { return xengine_tile_count(b->inst[i]->n_in, edge_of(b, i)); }
 // Tile edges instance i may take: a work item names its tile in 8 bits.
 bool tile_allowed(mwax_batch b, int i, int te) {
     return (te == kXTile || te == kXTileSmall) && xengine_tile_count(b->inst[i]->n_in, te) <= kXBatchMaxTiles;
@@ -361,7 +366,7 @@ void build_x_tables(mwax_batch b, const std::vector<std::vector<Segment>> &segs,
             x.ksplit = (int32_t)ceil_div(s.ngrp, x.kchunk);
             x.first = xa.first;
             x.i32 = xa.i32;
-            x.te = b->tile[i];
+            x.te = edge_of(b, i);
             const int nt = ntiles_of(b, i);
             const int d = (int)t.xd.size();
             t.xd.push_back(x);

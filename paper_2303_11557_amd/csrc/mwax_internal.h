@@ -273,6 +273,9 @@ int xengine_tile(int xprec);
 // Tile edges of the MFMA X-engine: single plans use kXTile; a batch instance
 // may use either (the autotuner picks).  Lower-triangle tiles per channel:
 constexpr int kXTile = 128, kXTileSmall = 64;
+// Plans of up to kXSmallInputs inputs run 32 x 32 blocks whose K loop a workgroup's
+// waves share, and so do FP16 batch instances (whose sums must be in a plan's order).
+constexpr int kXTileTiny = 32, kXSmallInputs = 64;
 int xengine_tile_count(int n_in, int te);
 
 // Persistent batched X-engine.  A work item is one 128 x 128 tile of one channel
@@ -295,7 +298,7 @@ struct XDesc {
     int32_t ksplit;         // chunks = ceil(ngrp / kchunk)
     int32_t first;          // as XArgs::first
     int32_t i32;            // as XArgs::i32
-    int32_t te;             // tile edge: kXTile or kXTileSmall
+    int32_t te;             // tile edge: kXTile, kXTileSmall or (FP16) kXTileTiny
 };
 constexpr int kXBatchMaxDesc = 256;
 constexpr int kXBatchMaxTiles = 256;

@@ -33,8 +33,8 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 
-constexpr int kTile = kXTile;       // tile edge in inputs (single-plan launches; a batch
-                                    // instance may take kTileSmall, see xengine_batch)
+constexpr int kTile = kXTile;       // tile edge in inputs (single-plan launches of more than
+                                    // kXSmallInputs; a batch instance may take kTileSmall)
 constexpr int kTileSmall = kXTileSmall;
 constexpr int kThreads = 256;       // 4 waves
 
@@ -54,21 +54,6 @@ __device__ __forceinline__ int xcd_logical(int b, int nb) {
     const int full = nb & ~7;
     if (b >= full) return b;
     return (b & 7) * (full >> 3) + (b >> 3);
-}
-
-// Per-byte two's-complement negation of four int8 values in [-127, 127].
-__device__ __forceinline__ uint32_t neg_i8x4(uint32_t x) {
-    const uint32_t nx = ~x;
-    return ((nx & 0x7F7F7F7Fu) + 0x01010101u) ^ (nx & 0x80808080u);
-}
-
-template <int XP>
-__device__ __forceinline__ uint4 negate16(uint4 v) {
-    if constexpr (XP == MWAX_X_INT8) {
-        return make_uint4(neg_i8x4(v.x), neg_i8x4(v.y), neg_i8x4(v.z), neg_i8x4(v.w));
-    } else {
-        return make_uint4(v.x ^ 0x80008000u, v.y ^ 0x80008000u, v.z ^ 0x80008000u, v.w ^ 0x80008000u);
-    }
 }
 
 template <int XP>
@@ -445,6 +430,161 @@ __global__ __launch_bounds__(kThreads, 2) void xengine_mfma(XArgs a) {
     else xengine_tile_loop<XP, kTile, true>(b, lds, c, rowA0, rowB0, wr, wc);
 }
 
+// ---------------------------------------------------------------------------
+// Small arrays (up to kXSmallInputs inputs): a 128-edge tile would leave most of a
+// workgroup's waves idle and a launch with one workgroup per channel, each behind
+// one long K loop.  Instead one workgroup runs one 32 x 32 block and its waves
+// share the K loop, straight from global memory (a row group of 32 inputs is 1 KB
+// contiguous; no panel is shared that LDS could hold).  The row groups are dealt in
+// stages of kSmallG to kSmallSlices slices; the slices' sums are added in order, in
+// int64 or FP64, so the result does not depend on how many waves share them: a
+// batch item (four waves) gives the same bits as a plan of its own (eight).
+// Bound by latency.  32 inputs, 128 channels, 10,000 spectra, channelise to emission,
+// 128-edge tiles / this: INT8 123 / 85 us, FP16 279 / 106 us; 64 inputs, 512 channels,
+// 4 x 64 spectra: INT8 189 / 131 us, FP16 115 / 83 us.
+// ---------------------------------------------------------------------------
+constexpr int kSmallSlices = 8, kSmallG = 8;
+template <int XP>
+using SmallSum = typename std::conditional<XP == MWAX_X_INT8, longlong2, double2>::type;
+
+// Fragments of kSmallG row groups of a block (rows from pa and pb), from group g0 on;
+// groups at or past gend read as zeros.
+struct SmallStage {
+    uint4 a[kSmallG], b[kSmallG];
+    __device__ __forceinline__ void fetch(const uint8_t *pa, const uint8_t *pb, int64_t gstride, int g0, int gend) {
+#pragma unroll
+        for (int k = 0; k < kSmallG; ++k) {
+            const int64_t o = (int64_t)min(g0 + k, gend - 1) * gstride;
+            a[k] = *reinterpret_cast<const uint4 *>(pa + o);
+            b[k] = *reinterpret_cast<const uint4 *>(pb + o);
+        }
+    }
+    template <int XP>
+    __device__ __forceinline__ void multiply(int g0, int gend, typename MfmaT<XP>::acc_t &re,
+                                             typename MfmaT<XP>::acc_t &im) const {
+        constexpr uint32_t kFlip = XP == MWAX_X_INT8 ? 0xffffffffu : 0x80008000u;
+        const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+        for (int k = 0; k < kSmallG; ++k) {
+            const bool in = g0 + k < gend;
+            const uint4 x = in ? a[k] : zero, y = in ? b[k] : zero;
+            re = MfmaT<XP>::mma(x, y, re);
+            im = MfmaT<XP>::mma(x, make_uint4(y.z ^ kFlip, y.w ^ kFlip, y.x, y.y), im);
+        }
+    }
+};
+
+// Block (I, J) of channel c over the segment of a, by the W waves of a workgroup;
+// sum: LDS for the running sums.  W = 1 takes segments of one stage.
+template <int XP, int W>
+__device__ __forceinline__ void small_block(const XArgs &a, int c, int I, int J, int wave, SmallSum<XP> (*sum)[64]) {
+    static_assert(kSmallSlices % W == 0, "whole passes of the slices");
+    using T = MfmaT<XP>;
+    using acc_t = typename T::acc_t;
+    using Sum = SmallSum<XP>;
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int64_t gstride = (int64_t)a.n_in * kRowBytes;
+    const uint8_t *base = a.chan + ((int64_t)c * a.NG + a.grp0) * gstride + half * 16;
+    const uint8_t *pa = base + min(I * 32 + l32, a.n_in - 1) * kRowBytes;
+    const uint8_t *pb = base + min(J * 32 + l32, a.n_in - 1) * kRowBytes;
+    // row r of the lane's sixteen sums
+    auto put = [&](int r, Sum v) {
+        const int n1 = I * 32 + (r >> 2) * 8 + half * 4 + (r & 3), n2 = J * 32 + l32;
+        if (n1 >= a.n_in || n2 > n1) return;
+        const int64_t e = (int64_t)c * a.P + (int64_t)n1 * (n1 + 1) / 2 + n2;
+        if (XP == MWAX_X_INT8 && a.i32) {
+            int2 *dst = reinterpret_cast<int2 *>(a.integ) + e;
+            int2 w = make_int2((int)v.x, (int)v.y);
+            if (!a.first) {
+                const int2 o = *dst;
+                w.x += o.x;
+                w.y += o.y;
+            }
+            *dst = w;
+        } else {
+            Sum *dst = reinterpret_cast<Sum *>(a.integ) + e;
+            if (!a.first) {
+                const Sum o = *dst;
+                v.x += o.x;
+                v.y += o.y;
+            }
+            *dst = v;
+        }
+    };
+    if constexpr (W == 1) {
+        acc_t re{}, im{};
+        SmallStage st;
+        st.fetch(pa, pb, gstride, 0, a.ngrp);
+        st.template multiply<XP>(0, a.ngrp, re, im);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            Sum v;
+            v.x = re[r];
+            v.y = im[r];
+            put(r, v);
+        }
+        return;
+    }
+    const int nst = (a.ngrp + kSmallG - 1) / kSmallG;
+#pragma unroll 1
+    for (int first = 0; first < min(kSmallSlices, nst); first += W) {
+        const int slice = first + wave;
+        acc_t re{}, im{};
+        Sum mine[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mine[r].x = mine[r].y = 0;
+        auto collect = [&] {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                mine[r].x += re[r];
+                mine[r].y += im[r];
+            }
+            re = acc_t{};
+            im = acc_t{};
+        };
+        SmallStage next;
+        if (slice < nst) next.fetch(pa, pb, gstride, slice * kSmallG, a.ngrp);
+        int groups = 0;
+        for (int s = slice; s < nst; s += kSmallSlices) {
+            const SmallStage cur = next;
+            if (s + kSmallSlices < nst) next.fetch(pa, pb, gstride, (s + kSmallSlices) * kSmallG, a.ngrp);
+            cur.template multiply<XP>(s * kSmallG, a.ngrp, re, im);
+            groups += kSmallG;
+            if (groups == T::kFlushGroups) {
+                collect();
+                groups = 0;
+            }
+        }
+        collect();
+#pragma unroll 1
+        for (int k = 0; k < W; ++k) {
+            if (wave == k) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    Sum v = mine[r];
+                    if (slice > 0) {
+                        v.x += sum[r][lane].x;
+                        v.y += sum[r][lane].y;
+                    }
+                    sum[r][lane] = v;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    for (int r = wave; r < 16; r += W) put(r, sum[r][lane]);
+}
+
+template <int XP, int W>
+__global__ __launch_bounds__(64 * W, 2) void xengine_small(XArgs a) {
+    __shared__ SmallSum<XP> sum[W > 1 ? 16 : 1][64];
+    const int lin = xcd_logical(blockIdx.x, gridDim.x);
+    const int c = lin / a.ntiles;
+    int I, J;
+    tile_ij(lin - c * a.ntiles, I, J);
+    small_block<XP, W>(a, c, I, J, __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), sum);
+}
+
 // One work item of the batched kernel: tile (I, J) of edge TE.  A wave is idle
 // on a diagonal tile above the diagonal, or when all its rows or columns lie past
 // the last input; it still stages data and meets the barriers.
@@ -501,7 +641,12 @@ __global__ __launch_bounds__(kThreads, 2) void xengine_batch(XBatchArgs b) {
             a.i32 = xd.i32;
             int I, J;
             tile_ij(t, I, J);
-            if (xd.te == kTileSmall) {
+            if (xd.te == kXTileTiny) {
+                if constexpr (XP == MWAX_X_FP16) {
+                    small_block<XP, 4>(a, c, I, J, wave, reinterpret_cast<SmallSum<XP> (*)[64]>(lds0));
+                    __syncthreads();   // the sums have been read
+                }
+            } else if (xd.te == kTileSmall) {
                 batch_tile<XP, kTileSmall>(a, lds, c, I, J, wr, wc, xd.ksplit > 1);
             } else {
                 batch_tile<XP, kTile>(a, lds, c, I, J, wr, wc, xd.ksplit > 1);
@@ -756,6 +901,88 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
                 }
                 *dst = v;
             }
+        }
+    }
+}
+
+// The averaging X-engine for few output channels or inputs (compare small_block):
+// one workgroup = one segment, one output channel and one 32 x 32 block; its eight
+// waves take units of up to kAvgUnit row groups of one fine channel in turn and add
+// the weighted partials to FP64 sums, which are added over the waves in order.
+// Bound by latency.  Channelise to emission, 64-edge form / this: 12 inputs, 1,024
+// channels by 16, FP16, 2 x 18,802 spectra 9,370 / 2,060 us; 18 inputs, 512 by 8,
+// INT8, 99,719 spectra 7,310 / 2,700 us.
+constexpr int kAvgUnit = 8 * kSmallG;
+template <int XP>
+__global__ __launch_bounds__(64 * kSmallSlices, 2) void xengine_avg_small(XAvgArgs a) {
+    __shared__ double2 sum[16][64];
+    using acc_t = typename MfmaT<XP>::acc_t;
+    const int lin = xcd_logical(blockIdx.x, gridDim.x);
+    const int os = lin / a.ntiles, seg = os / a.N, o = os - seg * a.N;
+    const XSeg sg = a.segs.s[seg];
+    int I, J;
+    tile_ij(lin - os * a.ntiles, I, J);
+    const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int h = a.F / 2, oc = a.N / 2;
+    const bool even = (a.F & 1) == 0, centre = a.F > 1 && o == oc;
+    const int nch = 2 * h + 1 - (centre ? 1 : 0);
+    const float inv_wsum = 1.0f / (centre ? (float)(a.F - 1) : (float)a.F);
+    const int64_t gstride = (int64_t)a.n_in * kRowBytes;
+    const int rowA = min(I * 32 + l32, a.n_in - 1) * kRowBytes + half * 16;
+    const int rowB = min(J * 32 + l32, a.n_in - 1) * kRowBytes + half * 16;
+    const int upc = (sg.ngrp + kAvgUnit - 1) / kAvgUnit, units = nch * upc;
+    double2 mine[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) mine[r] = make_double2(0.0, 0.0);
+    for (int u = wave; u < units; u += kSmallSlices) {
+        const int ci = u / upc, g0 = (u - ci * upc) * kAvgUnit, g1 = min(sg.ngrp, g0 + kAvgUnit);
+        const int d = -h + ci + (centre && ci >= h ? 1 : 0);
+        const int c = (((a.L / 2 + (o - oc) * a.F + d) % a.L) + a.L) % a.L;
+        float coef = (even && (d == -h || d == h) ? 0.5f : 1.0f) * inv_wsum;
+        if (sg.scales) coef *= sg.scales[c] * sg.scales[c];
+        const uint8_t *base = a.chan + ((int64_t)c * a.NG + sg.grp0) * gstride;
+        acc_t re{}, im{};
+        SmallStage next;
+        next.fetch(base + rowA, base + rowB, gstride, g0, g1);
+        for (int g = g0; g < g1; g += kSmallG) {
+            const SmallStage cur = next;
+            if (g + kSmallG < g1) next.fetch(base + rowA, base + rowB, gstride, g + kSmallG, g1);
+            cur.template multiply<XP>(g, g1, re, im);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            mine[r].x += (double)coef * (double)re[r];
+            mine[r].y += (double)coef * (double)im[r];
+        }
+    }
+#pragma unroll 1
+    for (int k = 0; k < kSmallSlices; ++k) {
+        if (wave == k) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                double2 v = mine[r];
+                if (k > 0) {
+                    v.x += sum[r][lane].x;
+                    v.y += sum[r][lane].y;
+                }
+                sum[r][lane] = v;
+            }
+        }
+        __syncthreads();
+    }
+    const int n2 = J * 32 + l32;
+    for (int r = wave; r < 16; r += kSmallSlices) {
+        const int n1 = I * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+        if (n1 < a.n_in && n2 <= n1) {
+            double2 *dst = reinterpret_cast<double2 *>(sg.integ) + (int64_t)o * a.P + (int64_t)n1 * (n1 + 1) / 2 + n2;
+            double2 v = sum[r][lane];
+            if (!sg.first) {
+                const double2 old = *dst;
+                v.x += old.x;
+                v.y += old.y;
+            }
+            *dst = v;
         }
     }
 }
@@ -1071,12 +1298,37 @@ void set_chunks(int xprec, XArgs &a) {
 }  // namespace
 
 bool xengine_accumulates(int xprec, const XArgs &args) {
+    if (args.n_in <= kXSmallInputs) return false;
     XArgs a = args;
     set_chunks(xprec, a);
     return a.nks > 1;
 }
 
+template <int XP>
+static hipError_t launch_xengine_small(const XArgs &args, hipStream_t s) {
+    XArgs a = args;
+    a.ntiles = xengine_tile_count(a.n_in, kXTileTiny);
+    const unsigned blocks = (unsigned)(a.ntiles * a.L);
+    // As many waves as the device holds at two per SIMD, but no more than stages and
+    // no fewer than two (one takes a single stage).  32 tiles FP16, 8,000 spectra x 2,
+    // whole step in us at 8 / 4 / 2 waves: 64 channels 182 / 204 / 263, 128 channels
+    // 360 / 355 / 385, 256 channels 702 / 723 / 685; 512 spectra x 2, 1,024 channels
+    // 359 / 308 / 289.
+    int w = kSmallSlices;
+    while (w > 1 && a.ngrp <= w / 2 * kSmallG) w /= 2;
+    while (w > 2 && (int64_t)blocks * w > 8 * device_cus()) w /= 2;
+    if (w == 1) hipLaunchKernelGGL((xengine_small<XP, 1>), dim3(blocks), dim3(64), 0, s, a);
+    else if (w == 2) hipLaunchKernelGGL((xengine_small<XP, 2>), dim3(blocks), dim3(128), 0, s, a);
+    else if (w == 4) hipLaunchKernelGGL((xengine_small<XP, 4>), dim3(blocks), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((xengine_small<XP, 8>), dim3(blocks), dim3(512), 0, s, a);
+    return hipGetLastError();
+}
+
 hipError_t launch_xengine(int xprec, const XArgs &args, hipStream_t s) {
+    if (args.n_in <= kXSmallInputs && args.ngrp > 0) {
+        if (xprec == MWAX_X_INT8) return launch_xengine_small<MWAX_X_INT8>(args, s);
+        if (xprec == MWAX_X_FP16) return launch_xengine_small<MWAX_X_FP16>(args, s);
+    }
     XArgs a = args;
     set_chunks(xprec, a);
     const int64_t blocks = (int64_t)a.ntiles * a.L * a.nks;
@@ -1131,6 +1383,19 @@ hipError_t launch_xengine_avg(int xprec, const XAvgArgs &args, hipStream_t s) {
     a.ntiles = tri_groups((a.n_in + kTileSmall - 1) / kTileSmall);
     if (a.segs.n < 1 || a.segs.n > kXSegs) return hipErrorInvalidValue;
     const int64_t blocks = (int64_t)a.N * a.ntiles * a.segs.n;
+    // Fewer 64-edge workgroups than CUs: waves that share the K loop instead.  Whole
+    // step in us, 64-edge form / this one, FP16, 200 spectra: 16 workgroups 244 / 90
+    // (64 inputs, 1,024 channels by 64), 128 workgroups 467 / 408 (64 inputs, 6,400
+    // by 50), 144 workgroups 325 / 213 (200 inputs, 1,024 by 64); but 256 workgroups
+    // 63 / 77 (64 inputs, 1,024 by 4) and 288 workgroups 62 / 82 (200 inputs, 256 by 8).
+    if (blocks < device_cus()) {
+        a.ntiles = xengine_tile_count(a.n_in, kXTileTiny);
+        const dim3 grid((unsigned)(a.N * a.ntiles * a.segs.n)), threads(64 * kSmallSlices);
+        if (xprec == MWAX_X_INT8) hipLaunchKernelGGL(xengine_avg_small<MWAX_X_INT8>, grid, threads, 0, s, a);
+        else if (xprec == MWAX_X_FP16) hipLaunchKernelGGL(xengine_avg_small<MWAX_X_FP16>, grid, threads, 0, s, a);
+        else return hipErrorInvalidValue;
+        return hipGetLastError();
+    }
     switch (xprec) {
         case MWAX_X_INT8:
             hipLaunchKernelGGL(xengine_avg<MWAX_X_INT8>, dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
