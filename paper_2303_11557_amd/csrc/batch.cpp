@@ -175,7 +175,8 @@ int edge_of(mwax_batch b, int i) {
 int ntiles_of(mwax_batch b, int i) { return xengine_tile_count(b->inst[i]->n_in, edge_of(b, i)); }
 // Tile edges instance i may take: a work item names its tile in 8 bits.
 bool tile_allowed(mwax_batch b, int i, int te) {
-    return (te == kXTile || te == kXTileSmall) && xengine_tile_count(b->inst[i]->n_in, te) <= kXBatchMaxTiles;
+    const int t = (b->inst[i]->n_in + te - 1) / te;
+    return (te == kXTile || te == kXTileSmall) && t * (t + 1) / 2 <= kXBatchMaxTiles;
 }
 
 // Whole-segment work items overwrite a slot with the first flush of each

@@ -219,8 +219,8 @@ struct XArgs {
     int32_t ngrp;           // groups in the segment
     int32_t n_in;
     int32_t L;
-    int32_t ntiles;         // lower-triangle tiles per channel
-    int32_t tile;           // tile edge (rows)
+    int32_t ntiles;         // workgroups per channel (set by the launch)
+    int32_t sets;           // diagonal tiles packed four to three workgroups: sets of four
     void *integ;            // this slot's integrators [L][P][2] (int64 or double)
     int64_t P;
     int32_t nks;            // chunks of row groups per tile (set by launch_xengine;
@@ -269,13 +269,13 @@ hipError_t launch_xengine(int xprec, const XArgs &a, hipStream_t s);
 // into chunks); false if the first flush of a segment that starts
 // its integration overwrites them.
 bool xengine_accumulates(int xprec, const XArgs &a);
-int xengine_tile(int xprec);
 // Tile edges of the MFMA X-engine: single plans use kXTile; a batch instance
-// may use either (the autotuner picks).  Lower-triangle tiles per channel:
+// may use either (the autotuner picks).
 constexpr int kXTile = 128, kXTileSmall = 64;
 // Plans of up to kXSmallInputs inputs run 32 x 32 blocks whose K loop a workgroup's
 // waves share, and so do FP16 batch instances (whose sums must be in a plan's order).
 constexpr int kXTileTiny = 32, kXSmallInputs = 64;
+// Workgroups per channel at a tile edge.
 int xengine_tile_count(int n_in, int te);
 
 // Persistent batched X-engine.  A work item is one 128 x 128 tile of one channel

@@ -33,7 +33,7 @@ struct mwax_plan_s {
     mwax_dims d{};
     hipStream_t stream = nullptr;
     int device = 0;
-    int L = 0, G = 0, n_in = 0, xprec = 0, R = 1, ntiles = 0;
+    int L = 0, G = 0, n_in = 0, xprec = 0, R = 1;
     int64_t T = 0, P = 0;
 
     uint8_t *chan = nullptr;

@@ -259,8 +259,6 @@ XArgs mwax::xengine_args(mwax_plan p, const Segment &s) {
     a.ngrp = (int32_t)s.ngrp;
     a.n_in = p->n_in;
     a.L = p->L;
-    a.ntiles = p->ntiles;
-    a.tile = xengine_tile(p->xprec);
     a.integ = (uint8_t *)p->integ + (size_t)s.slot * p->slot_bytes;
     a.P = p->P;
     a.first = s.local0 == 0;
@@ -355,8 +353,6 @@ mwax_status create_plan(const mwax_config *cfg, void *hip_stream, mwax_plan *out
         delete p;
         return r;
     }
-    const int nt = (p->n_in + xengine_tile(p->xprec) - 1) / xengine_tile(p->xprec);
-    p->ntiles = nt * (nt + 1) / 2;
     const int64_t segs = (d.max_spectra + p->T - 1) / p->T + 1;
     p->NG = (d.max_spectra + p->G - 1) / p->G + segs;
     p->integ32 = integ_elem_bytes(p->xprec, p->T) == 8;

@@ -13,8 +13,8 @@
 // wasted on the real expansion.  Each 16-byte half of a row holds the real
 // parts of 8 (FP16: 4) frames followed by their imaginary parts, so B is made
 // from A in registers by swapping the two 8-byte quarters of a half and
-// negating one of them.  Work is split into 128 x 128 tiles of the lower
-// triangle.
+// negating one of them.  Work is split into 64 x 64 blocks of the lower triangle,
+// four to a workgroup.
 //
 //   INT8: v_mfma_i32_32x32x32_i8, int32 partials flushed to int64 integrators
 //         at most every 65536 spectra (|partial| < 518160 * 4096 < 2^31).
@@ -45,6 +45,60 @@ __device__ __forceinline__ void tile_ij(int t, int &I, int &J) {
     while (i * (i + 1) / 2 > t) --i;
     I = i;
     J = t - i * (i + 1) / 2;
+}
+
+// Lower triangle of m x m blocks, one block per wave, four to a workgroup.
+// Workgroup t of a channel, with nt = m / 2 tiles of 2 x 2 blocks along an edge:
+//   t < nt (nt - 1) / 2: the four blocks of an off-diagonal tile;
+//   then, for each of g sets of four diagonal tiles (three blocks each), three
+//   workgroups: the blocks of one tile and one block of the set's last tile;
+//   then the diagonal tiles left, three blocks and an idle wave each;
+//   for odd m, the last row of blocks, three columns to a workgroup, its diagonal
+//   block with the last of them.
+// An idle wave does not only leave its SIMD empty: the other SIMDs, which have
+// more to do, hold back the waves it would run instead.
+// Four LDS slots hold the rows of a block each; wave w copies slot w.
+struct TriBlock {
+    int ra, rb;          // row blocks of the wave's rows and columns (ra >= rb), or ra < 0: idle
+    int sa, sb;          // the slots that hold them
+    int copy;            // row block this wave copies into its slot
+};
+__host__ __device__ inline int tri_sets(int m) { return m / 8; }
+__host__ __device__ inline int tri_groups(int m, int g) {
+    const int nt = m / 2, strips = (m + 1) / 3 > 1 ? (m + 1) / 3 : 1;
+    return nt * (nt - 1) / 2 + nt - g + (m & 1 ? strips : 0);
+}
+__device__ __forceinline__ TriBlock tri_block(int m, int g, int t, int role, int wave) {
+    const int nt = m / 2, noff = nt * (nt - 1) / 2;
+    TriBlock b;
+    if (t < noff) {
+        int I, J;
+        tile_ij(t, I, J);
+        ++I;
+        b.ra = 2 * I + (role >> 1), b.rb = 2 * J + (role & 1);
+        b.sa = role >> 1, b.sb = 2 + (role & 1);
+        b.copy = wave < 2 ? 2 * I + wave : 2 * J + (wave & 1);
+        return b;
+    }
+    const int u = t - noff, w = u - (nt - g);
+    if (w >= 0) {
+        const int r = m - 1, col = 3 * w + role;
+        const bool diag = role == 3 && 3 * w + 3 >= r;
+        b.ra = diag || (role < 3 && col < r) ? r : -1, b.rb = diag ? r : col;
+        b.sa = 0, b.sb = diag ? 0 : 1 + role;
+        b.copy = wave == 0 ? r : min(3 * w + wave - 1, r);
+        return b;
+    }
+    const int j = u % 3;
+    const bool group = u < 3 * g;
+    const int d = group ? u / 3 * 4 + j : 4 * g + (u - 3 * g), e = group ? u / 3 * 4 + 3 : d;
+    // blocks of a diagonal tile: 0 (0, 0), 1 (1, 0), 2 (1, 1)
+    const int k = role < 3 ? role : j, x = role < 3 ? d : e, s0 = role < 3 ? 0 : 2;
+    b.ra = 2 * x + (k > 0), b.rb = 2 * x + (k > 1);
+    b.sa = s0 + (k > 0), b.sb = s0 + (k > 1);
+    if (role == 3 && !group) b.ra = -1;
+    b.copy = 2 * (wave < 2 ? d : e) + (wave & 1);
+    return b;
 }
 
 // Workgroups are handed to the 8 XCDs round-robin.  Renumber them so the
@@ -84,19 +138,23 @@ struct MfmaT<MWAX_X_FP16> {
     }
 };
 
-// One workgroup = one channel x one 128 x 128 tile of the lower triangle.
-// Four waves in a 2 x 2 layout, 64 x 64 outputs (2 x 2 blocks of 32 x 32) each,
-// real and imaginary accumulators for every block (128 accumulator registers).
+// One workgroup = one channel x four 64 x 64 blocks of the lower triangle (see
+// TriBlock; off the diagonal a 128 x 128 tile), one per wave in 2 x 2 parts of
+// 32 x 32, with real and imaginary accumulators for every part (128 accumulator
+// registers).  Channelise to emission, 128 x 128 tiles only / this: INT8, 512 inputs,
+// 80,000 spectra 11.22 / 10.99 ms; 140 inputs, 20,000 spectra 739 / 680 us; FP16, 186
+// inputs, 1,024 channels, 1,250 spectra 1,067 / 1,024 us; 440 inputs, 5,000 spectra
+// 1,155 / 1,084 us.
 // Two workgroups share a CU (two waves per SIMD), so one workgroup's barrier
 // latency is covered by the other's matrix work.
 //
 // The K loop runs over stages of kXG row groups.  Stages are copied from global
 // memory straight into LDS (16 bytes per lane, no register staging and no LDS
 // store instructions) into a ring of kNBuf stage buffers, kDist stages
-// ahead of the matrix work, with one barrier per stage.  Each wave copies 32
-// whole rows (1 KB of global memory) of each panel into one LDS block laid out
-// [16-byte half][row], the layout the fragment reads want.  The ring buffers are separate LDS
-// objects, so the compiler can tell a read of one buffer from the copies still
+// ahead of the matrix work, with one barrier per stage.  Each wave copies the
+// rows of one slot, 32 whole rows (1 KB of global memory) at a time into an LDS block
+// laid out [16-byte half][row], the layout the fragment reads want.  The ring buffers
+// are separate LDS objects, so the compiler can tell a read of one buffer from the copies still
 // landing in the others and does not wait for those.
 //
 // The Im operand B2 is formed in registers from the B fragment: its two 8-byte
@@ -116,8 +174,8 @@ static_assert((kNBuf == 2 || kNBuf == 4) && kDist >= 1 && kDist < kNBuf, "ring o
 
 // Stage geometry of a TE x TE tile (TE = 128 or 64).  A 128-edge tile gives each
 // of the four waves 64 x 64 outputs (2 x 2 blocks of 32 x 32) and each wave
-// copies 32 rows of both panels; a 64-edge tile gives each wave one 32 x 32
-// block and each wave copies 32 rows of one panel.
+// copies 64 rows; a 64-edge tile gives each wave one 32 x 32 block and each wave
+// copies 32 rows.
 template <int TE, int DIST = kDist>
 struct TileGeo {
     static_assert(TE == 128 || TE == 64, "tile edge");
@@ -126,7 +184,9 @@ struct TileGeo {
     static constexpr int kGroupPitch = TE / 32 * kBlock;
     static constexpr int kPanel = kXG * kGroupPitch;     // one panel (A or B) of a stage
     static constexpr int kStage = 2 * kPanel;
-    static constexpr int kCopiesPerStage = (TE == 128 ? 2 : 1) * kXG;   // copies per wave per stage
+    // first byte of slot w (TE / 2 rows) in a row group: two slots to a panel
+    __host__ __device__ static constexpr int slot(int w) { return (w >> 1) * kPanel + (w & 1) * MB * kBlock; }
+    static constexpr int kCopiesPerStage = MB * kXG;     // copies per wave per stage
     // s_waitcnt immediate: vmcnt(copies of the DIST - 1 later stages), lgkmcnt(0)
     static constexpr int kWaitCopies = kCopiesPerStage * (DIST - 1);
     static_assert(kWaitCopies < 16, "vmcnt immediate");
@@ -155,12 +215,11 @@ __device__ __forceinline__ void stage_barrier() {
 
 // ATOMIC: flush with int64 atomic adds (another workgroup may be flushing other
 // row groups of the same tile at the same time).
-template <int XP, int TE, bool ACTIVE, bool ATOMIC = false>
-__device__ __forceinline__ void xengine_tile_loop(const XArgs &a, const XLds &lds, int c, int rowA0, int rowB0,
-                                                  int wr, int wc) {
+template <int XP, int TE, bool ACTIVE, bool ATOMIC, bool BATCH>
+__device__ __forceinline__ void xengine_tile_loop(const XArgs &a, const XLds &lds, int c, const TriBlock &tb) {
     static_assert(!ATOMIC || XP == MWAX_X_INT8, "atomic flushes are exact for integer partials only");
     using GEO = TileGeo<TE>;
-    constexpr int MB = GEO::MB, kGroupPitch = GEO::kGroupPitch, kPanel = GEO::kPanel;
+    constexpr int MB = GEO::MB, kGroupPitch = GEO::kGroupPitch;
     using T = MfmaT<XP>;
     using acc_t = typename T::acc_t;
     constexpr bool INT8 = XP == MWAX_X_INT8;
@@ -168,21 +227,19 @@ __device__ __forceinline__ void xengine_tile_loop(const XArgs &a, const XLds &ld
     const int half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
 
-    // Copies: wave w moves rows w * 32 .. w * 32 + 31 of both panels (TE = 128),
-    // or rows (w % 2) * 32 .. + 31 of panel w / 2 (TE = 64); lane l takes half
-    // l / 32 of its row and lands at byte l * 16 of the row's block.
+    // Copies: wave w moves the TE / 2 rows of slot w, 32 at a time; lane l takes half
+    // l / 32 of its row and lands at byte l * 16 of the rows' block.
     // Rows past the last input are read from a clamped (valid) address and not
     // cleared: row i of A and column j of B reach only output (i, j), and outputs
     // past the last input are never flushed.
-    const int cblk = TE == 128 ? wave : (wave & 1);          // block within the panel
-    const int cpanel = TE == 128 ? 0 : (wave >> 1) * kPanel;  // TE = 64: the panel this wave copies
-    const int chalf = lane >> 5, crow = cblk * 32 + (lane & 31);
-    const uint32_t offA = (uint32_t)min(rowA0 + crow, a.n_in - 1) * kRowBytes + chalf * 16;
-    const uint32_t offB = (uint32_t)min(rowB0 + crow, a.n_in - 1) * kRowBytes + chalf * 16;
-    const uint32_t offZ = (uint32_t)crow * kRowBytes + chalf * 16;
+    uint32_t off[MB];
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+        off[m] = (uint32_t)min((tb.copy * MB + m) * 32 + l32, a.n_in - 1) * kRowBytes + half * 16;
+    const uint32_t offZ = (uint32_t)l32 * kRowBytes + half * 16;
     const int64_t gstride = (int64_t)a.n_in * kRowBytes;   // bytes between row groups
     const uint8_t *base = a.chan + ((int64_t)c * a.NG + a.grp0) * gstride;
-    const int ldst = cpanel + cblk * kBlock;
+    const int ldst = GEO::slot(wave);
     const int nstages = (a.ngrp + kXG - 1) / kXG;
 
     // CHECK: the stage may reach past the segment end (its last stage)
@@ -193,23 +250,18 @@ __device__ __forceinline__ void xengine_tile_loop(const XArgs &a, const XLds &ld
             const int g = s * kXG + k;
             const bool in = !CHECK || g < a.ngrp;
             const uint8_t *gb = in ? base + (int64_t)g * gstride : kZeroGroup;
-            if constexpr (TE == 128) {
-                __builtin_amdgcn_global_load_lds(gb + (in ? offA : offZ), buf + k * kGroupPitch + ldst, 16, 0, 0);
-                __builtin_amdgcn_global_load_lds(gb + (in ? offB : offZ), buf + kPanel + k * kGroupPitch + ldst, 16,
-                                                 0, 0);
-            } else {
-                // waves 0, 1 copy the A panel, waves 2, 3 the B panel
-                const uint32_t off = in ? (wave < 2 ? offA : offB) : offZ;
-                __builtin_amdgcn_global_load_lds(gb + off, buf + k * kGroupPitch + ldst, 16, 0, 0);
-            }
+#pragma unroll
+            for (int m = 0; m < MB; ++m)
+                __builtin_amdgcn_global_load_lds(gb + (in ? off[m] : offZ), buf + k * kGroupPitch + ldst + m * kBlock,
+                                                 16, 0, 0);
         }
     };
 
     acc_t re[MB][MB], im[MB][MB];
-    // fragment m of a wave's 32 MB rows is block MB * w + m; lane (half, l32)
-    // reads half `half` of its row l32
-    const int fa_off = wr * MB * kBlock + half * 512 + l32 * 16;
-    const int fb_off = kPanel + wc * MB * kBlock + half * 512 + l32 * 16;
+    // fragment m of a slot's 32 MB rows is its block m; lane (half, l32) reads half
+    // `half` of its row l32
+    const int fa_off = GEO::slot(tb.sa) + half * 512 + l32 * 16;
+    const int fb_off = GEO::slot(tb.sb) + half * 512 + l32 * 16;
     constexpr uint32_t kFlip = INT8 ? 0xffffffffu : 0x80008000u;
 
     // One stage of matrix-core work from one buffer; the fragments of row group
@@ -325,21 +377,20 @@ __device__ __forceinline__ void xengine_tile_loop(const XArgs &a, const XLds &ld
             // opaque here so the compiler cannot hoist 64 integrator addresses out of
             // the K loop (they would occupy half the register file).
             uint8_t *ibase = reinterpret_cast<uint8_t *>(a.integ);
-            int fr0 = rowA0, fc0 = rowB0;
-            asm volatile("" : "+s"(ibase), "+s"(fr0), "+s"(fc0));
+            int fr0 = tb.ra * (TE / 2), fc0 = tb.rb * (TE / 2);
+            if constexpr (BATCH) asm volatile("" : "+v"(ibase), "+v"(fr0), "+v"(fc0));
+            else asm volatile("" : "+s"(ibase), "+v"(fr0), "+v"(fc0));
             // the first flush of a segment that starts its integration writes the
             // integrators instead of adding to them (no read)
             const bool store = a.first && s0 == 0;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) {
-                const int RB = wr * MB + mb;
 #pragma unroll
                 for (int nb2 = 0; nb2 < MB; ++nb2) {
-                    const int CB = wc * MB + nb2;
-                    const int n2 = fc0 + CB * 32 + l32;
+                    const int n2 = fc0 + nb2 * 32 + l32;
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
-                        const int n1 = fr0 + RB * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+                        const int n1 = fr0 + mb * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
                         if (n1 < a.n_in && n2 <= n1) {
                             const int64_t p = (int64_t)n1 * (n1 + 1) / 2 + n2;
                             if constexpr (ATOMIC) {
@@ -394,6 +445,21 @@ __device__ __forceinline__ void xengine_tile_loop(const XArgs &a, const XLds &ld
     __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
 }
 
+// The wave's block of a workgroup; an idle wave still copies its slot and meets the
+// barriers.
+template <int XP, int TE, bool BATCH>
+__device__ __forceinline__ void run_blocks(const XArgs &a, const XLds &lds, int c, const TriBlock &tb, bool atomic) {
+    if constexpr (XP == MWAX_X_INT8) {
+        if (atomic) {
+            if (tb.ra < 0) xengine_tile_loop<XP, TE, false, true, BATCH>(a, lds, c, tb);
+            else xengine_tile_loop<XP, TE, true, true, BATCH>(a, lds, c, tb);
+            return;
+        }
+    }
+    if (tb.ra < 0) xengine_tile_loop<XP, TE, false, false, BATCH>(a, lds, c, tb);
+    else xengine_tile_loop<XP, TE, true, false, BATCH>(a, lds, c, tb);
+}
+
 // Workgroup -> (chunk, channel, tile): the tiles of one channel are consecutive,
 // so they land on one XCD and share its L2; the chunks of a tile read disjoint
 // row groups and run one after another (measured: 25 % less HBM traffic than
@@ -408,26 +474,14 @@ __global__ __launch_bounds__(kThreads, 2) void xengine_mfma(XArgs a) {
     const int ks = lin / per_k;
     const int rem = lin - ks * per_k;
     const int c = rem / a.ntiles, t = rem - c * a.ntiles;
-    int I, J;
-    tile_ij(t, I, J);
-    const int rowA0 = I * kTile, rowB0 = J * kTile;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wr = wave >> 1, wc = wave & 1;
+    // the wave of each block turns with the workgroup: an idle one is on another
+    // SIMD from workgroup to workgroup
+    const TriBlock tb = tri_block((a.n_in + 63) / 64, a.sets, t, (wave + lin) & 3, wave);
     XArgs b = a;
     b.grp0 = a.grp0 + (int64_t)ks * a.kchunk;
     b.ngrp = min(a.kchunk, a.ngrp - ks * a.kchunk);
-    // A wave is idle on a diagonal tile above the diagonal, or when all its rows or
-    // columns lie past the last input; it still stages data and meets the barriers.
-    const bool idle = (I == J && wr < wc) || rowA0 + wr * 64 >= a.n_in || rowB0 + wc * 64 >= a.n_in;
-    if constexpr (XP == MWAX_X_INT8) {
-        if (a.nks > 1) {
-            if (idle) xengine_tile_loop<XP, kTile, false, true>(b, lds, c, rowA0, rowB0, wr, wc);
-            else xengine_tile_loop<XP, kTile, true, true>(b, lds, c, rowA0, rowB0, wr, wc);
-            return;
-        }
-    }
-    if (idle) xengine_tile_loop<XP, kTile, false>(b, lds, c, rowA0, rowB0, wr, wc);
-    else xengine_tile_loop<XP, kTile, true>(b, lds, c, rowA0, rowB0, wr, wc);
+    run_blocks<XP, kTile, false>(b, lds, c, tb, a.nks > 1);
 }
 
 // ---------------------------------------------------------------------------
@@ -585,25 +639,6 @@ __global__ __launch_bounds__(64 * W, 2) void xengine_small(XArgs a) {
     small_block<XP, W>(a, c, I, J, __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), sum);
 }
 
-// One work item of the batched kernel: tile (I, J) of edge TE.  A wave is idle
-// on a diagonal tile above the diagonal, or when all its rows or columns lie past
-// the last input; it still stages data and meets the barriers.
-template <int XP, int TE>
-__device__ __forceinline__ void batch_tile(const XArgs &a, const XLds &lds, int c, int I, int J, int wr, int wc,
-                                           bool atomic) {
-    const int rowA0 = I * TE, rowB0 = J * TE;
-    const bool idle = (I == J && wr < wc) || rowA0 + wr * (TE / 2) >= a.n_in || rowB0 + wc * (TE / 2) >= a.n_in;
-    if constexpr (XP == MWAX_X_INT8) {
-        if (atomic) {
-            if (idle) xengine_tile_loop<XP, TE, false, true>(a, lds, c, rowA0, rowB0, wr, wc);
-            else xengine_tile_loop<XP, TE, true, true>(a, lds, c, rowA0, rowB0, wr, wc);
-            return;
-        }
-    }
-    if (idle) xengine_tile_loop<XP, TE, false>(a, lds, c, rowA0, rowB0, wr, wc);
-    else xengine_tile_loop<XP, TE, true>(a, lds, c, rowA0, rowB0, wr, wc);
-}
-
 // Persistent batched form (see XBatchArgs): each workgroup takes items from the
 // queue of its XCD until it is empty, then from the other queues in turn, and
 // exits when all are empty.  Every item is one tile of one channel over one chunk
@@ -614,7 +649,6 @@ __global__ __launch_bounds__(kThreads, 2) void xengine_batch(XBatchArgs b) {
     __shared__ int s_item;
     const XLds lds{{lds0, lds1, lds2, lds3}};
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wr = wave >> 1, wc = wave & 1;
     const int home = blockIdx.x & (kXQueues - 1);
     for (int v = 0; v < kXQueues; ++v) {
         const int q = (home + v) & (kXQueues - 1);
@@ -639,64 +673,27 @@ __global__ __launch_bounds__(kThreads, 2) void xengine_batch(XBatchArgs b) {
             a.P = xd.P;
             a.first = xd.first;
             a.i32 = xd.i32;
-            int I, J;
-            tile_ij(t, I, J);
             if (xd.te == kXTileTiny) {
                 if constexpr (XP == MWAX_X_FP16) {
+                    int I, J;
+                    tile_ij(t, I, J);
                     small_block<XP, 4>(a, c, I, J, wave, reinterpret_cast<SmallSum<XP> (*)[64]>(lds0));
                     __syncthreads();   // the sums have been read
                 }
             } else if (xd.te == kTileSmall) {
-                batch_tile<XP, kTileSmall>(a, lds, c, I, J, wr, wc, xd.ksplit > 1);
+                const TriBlock tb = tri_block((a.n_in + 31) / 32, tri_sets((a.n_in + 31) / 32), t, (wave + k) & 3, wave);
+                run_blocks<XP, kTileSmall, true>(a, lds, c, tb, xd.ksplit > 1);
             } else {
-                batch_tile<XP, kTile>(a, lds, c, I, J, wr, wc, xd.ksplit > 1);
+                const TriBlock tb = tri_block((a.n_in + 63) / 64, tri_sets((a.n_in + 63) / 64), t, (wave + k) & 3, wave);
+                run_blocks<XP, kTile, true>(a, lds, c, tb, xd.ksplit > 1);
             }
         }
     }
 }
 
-// Lower triangle in 32 x 32 blocks, four to a workgroup (one per wave), for the
-// kernels on 64-edge tiles (nt of them along an edge).  Workgroup t of a channel:
-//   t < nt (nt - 1) / 2: the four blocks of an off-diagonal tile;
-//   then, for every four diagonal tiles (three blocks each), three workgroups: the
-//   blocks of one tile and one block of the group's last tile;
-//   then the diagonal tiles left (nt mod 4), three blocks and an idle wave each.
-// An idle wave does not only leave its SIMD empty: the other SIMDs, which have
-// more to do, hold back the waves it would run instead.
-// Four LDS slots hold 32 rows each; wave w copies slot w.
-struct TriBlock {
-    int ra, rb;          // row blocks of the wave's rows and columns (ra >= rb), or ra < 0: idle
-    int sa, sb;          // the slots that hold them
-    int copy;            // row block this wave copies into its slot
-};
-__host__ __device__ inline int tri_groups(int nt) { return nt * (nt - 1) / 2 + 3 * (nt / 4) + nt % 4; }
-__device__ __forceinline__ TriBlock tri_block(int nt, int t, int role, int wave) {
-    const int noff = nt * (nt - 1) / 2;
-    TriBlock b;
-    if (t < noff) {
-        int I, J;
-        tile_ij(t, I, J);
-        ++I;
-        b.ra = 2 * I + (role >> 1), b.rb = 2 * J + (role & 1);
-        b.sa = role >> 1, b.sb = 2 + (role & 1);
-        b.copy = wave < 2 ? 2 * I + wave : 2 * J + (wave & 1);
-        return b;
-    }
-    const int u = t - noff, g = nt / 4, j = u % 3;
-    const bool group = u < 3 * g;
-    const int d = group ? u / 3 * 4 + j : 4 * g + (u - 3 * g), e = group ? u / 3 * 4 + 3 : d;
-    // blocks of a diagonal tile: 0 (0, 0), 1 (1, 0), 2 (1, 1)
-    const int k = role < 3 ? role : j, x = role < 3 ? d : e, s0 = role < 3 ? 0 : 2;
-    b.ra = 2 * x + (k > 0), b.rb = 2 * x + (k > 1);
-    b.sa = s0 + (k > 0), b.sb = s0 + (k > 1);
-    if (role == 3 && !group) b.ra = -1;
-    b.copy = 2 * (wave < 2 ? d : e) + (wave & 1);
-    return b;
-}
-
 // ---------------------------------------------------------------------------
 // Averaging X-engine (Sec. 2.6 applied inside the correlation): one workgroup =
-// one output channel o of N = L / F x one 64 x 64 tile.  It correlates the fine
+// one output channel o of N = L / F x four 32 x 32 blocks.  It correlates the fine
 // channels of o one after another -- offsets |d| <= F / 2 around o's centre
 // (the rule of average.hip: the outermost pair at weight 1/2 for even F, DC left
 // out of the centre channel) -- with the MFMA K loop running over the
@@ -741,8 +738,8 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
     const int lane = threadIdx.x & 63;
     const int half = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const TriBlock tb = tri_block((a.n_in + TE - 1) / TE, lin - os * a.ntiles, (wave + lin) & 3, wave);
-    const bool active = tb.ra >= 0 && tb.ra * 32 < a.n_in;
+    const TriBlock tb = tri_block((a.n_in + 31) / 32, tri_sets((a.n_in + 31) / 32), lin - os * a.ntiles, (wave + lin) & 3, wave);
+    const bool active = tb.ra >= 0;
 
     // the fine channels of o: offsets d = -h .. h (DC skipped in the centre one),
     // channel (L/2 + (o - N/2) F + d) mod L.  They are walked with cursors: no
@@ -1047,8 +1044,8 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_f32(XArgs a, XSegList seg
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     // the wave of each block turns with the workgroup: an idle one is on another
     // SIMD from workgroup to workgroup
-    const TriBlock tb = tri_block((a.n_in + kFT - 1) / kFT, lin - cs * a.ntiles, (wave + lin) & 3, wave);
-    const bool active = tb.ra >= 0 && tb.ra * 32 < a.n_in;
+    const TriBlock tb = tri_block((a.n_in + 31) / 32, tri_sets((a.n_in + 31) / 32), lin - cs * a.ntiles, (wave + lin) & 3, wave);
+    const bool active = tb.ra >= 0;
 
     // copies: wave w moves the 32 rows of slot w.  Rows past the last input are read
     // from a clamped address: they reach only outputs that are never flushed.
@@ -1236,8 +1233,11 @@ __global__ __launch_bounds__(64 * kFSWaves, 2) void xengine_f32_small(XArgs a, X
 
 }  // namespace
 
-int xengine_tile(int) { return kTile; }
 int xengine_tile_count(int n_in, int te) {
+    if (te != kXTileTiny) {
+        const int m = (n_in + te / 2 - 1) / (te / 2);
+        return tri_groups(m, tri_sets(m));
+    }
     const int t = (n_in + te - 1) / te;
     return t * (t + 1) / 2;
 }
@@ -1288,10 +1288,25 @@ int pick_chunks(int64_t items, int ngrp, int slots) {
 }  // namespace
 
 namespace {
-// Chunks per tile of a single-plan launch (INT8 only; a.nks == 1 on entry asks
-// for whole segments) and their size.
+// Workgroups per channel of a single-plan launch, chunks per workgroup (INT8 only;
+// a.nks == 1 on entry asks for whole segments) and their size.
 void set_chunks(int xprec, XArgs &a) {
+    const int m = (a.n_in + kTile / 2 - 1) / (kTile / 2);
+    a.sets = tri_sets(m);
+    a.ntiles = tri_groups(m, a.sets);
     if (a.nks != 1) a.nks = xprec == MWAX_X_INT8 ? pick_chunks((int64_t)a.ntiles * a.L, a.ngrp, resident_slots()) : 1;
+    // Unsplit, the last round of workgroups is shorter with some waves idle if that
+    // brings as many workgroups to every CU (each has the same number of blocks then).
+    // FP16, 512 inputs, 128 channels, two calls of 10,000 spectra: 10 workgroups per
+    // channel, five per CU, 4,724 us channelise to emission; 9, 4.5 per CU, 4,751 us.
+    if (a.nks == 1) {
+        const int cus = device_cus(), alone = tri_groups(m, 0);
+        auto most_blocks = [&](int64_t n) { return (double)((n * a.L + cus - 1) / cus) / (double)n; };
+        if (most_blocks(alone) < most_blocks(a.ntiles)) {
+            a.sets = 0;
+            a.ntiles = alone;
+        }
+    }
     a.kchunk = (a.ngrp + a.nks - 1) / a.nks;
     a.nks = (a.ngrp + a.kchunk - 1) / a.kchunk;   // no empty chunk
 }
@@ -1349,7 +1364,7 @@ hipError_t launch_xengine(int xprec, const XArgs &args, hipStream_t s) {
 hipError_t launch_xengine_f32(const XArgs &args, const XSegList &segs, hipStream_t s) {
     XArgs a = args;
     if (segs.n < 1 || segs.n > kXSegs) return hipErrorInvalidValue;
-    a.ntiles = tri_groups((a.n_in + kFT - 1) / kFT);
+    a.ntiles = xengine_tile_count(a.n_in, kXTileSmall);
     const int64_t tiles = (int64_t)a.ntiles * a.L * segs.n;
     // fewer 64 x 64 tiles than the four per CU that are resident together
     // would leave matrix cores idle; the small form has twice the waves per
@@ -1380,7 +1395,7 @@ hipError_t launch_xengine_batch(int xprec, const XBatchArgs &b, int grid, hipStr
 
 hipError_t launch_xengine_avg(int xprec, const XAvgArgs &args, hipStream_t s) {
     XAvgArgs a = args;
-    a.ntiles = tri_groups((a.n_in + kTileSmall - 1) / kTileSmall);
+    a.ntiles = xengine_tile_count(a.n_in, kXTileSmall);
     if (a.segs.n < 1 || a.segs.n > kXSegs) return hipErrorInvalidValue;
     const int64_t blocks = (int64_t)a.N * a.ntiles * a.segs.n;
     // Fewer 64-edge workgroups than CUs: waves that share the K loop instead.  Whole
