@@ -5,9 +5,12 @@
 // Occupancy.  Flags mark, per input and per 50 ms sub-block, the sub-blocks
 // whose samples were zeroed.  The weight of pair (n1, n2) in integration j is
 // the fraction of j's sub-blocks populated in both inputs.  Each workgroup
-// owns a 64 x 64 block of the pair triangle: it packs the populated flags of
-// its 64 + 64 inputs into 32-bit masks in LDS, 1024 sub-blocks at a time, and
-// every thread counts 4 x 4 pairs with AND + popcount.  No workspace.
+// owns a 32 x 32 block of the pair triangle: it packs the populated flags of
+// its 32 + 32 inputs into 32-bit masks in LDS, 1024 sub-blocks at a time, and
+// every thread counts 2 x 2 pairs with AND + popcount.  No workspace.  Bound by
+// the latency of the flag loads: a wave has all its rows in flight at once.
+// 512 inputs, 160 sub-blocks: 7.6 us (64 x 64 blocks with 8 of a wave's 32 rows in
+// flight: 16.4 us).
 //
 // Normalisation.  V[j][c][p] /= w[j][p] where w > 0; where w == 0 every
 // product in the sum had a zeroed factor, so V is already 0 and is left as it
@@ -21,11 +24,11 @@
 namespace mwax {
 namespace {
 
-constexpr int kWBlock = 64;          // inputs per side of a pair block
+constexpr int kWBlock = 32;          // inputs per side of a pair block
 constexpr int kWWords = 32;          // mask words per LDS pass (1024 sub-blocks)
 constexpr int kMaxInputs = 2048;     // n_inputs of a 1024-tile array
-constexpr int kRowBatch = 8;         // flag rows a wave loads before their ballots
-static_assert(2 * kWBlock % (4 * kRowBatch) == 0, "row batches must tile the 128 rows");
+constexpr int kRowBatch = 16;        // flag rows a wave loads before their ballots
+static_assert(2 * kWBlock % (4 * kRowBatch) == 0, "row batches must tile the 64 rows");
 
 __global__ __launch_bounds__(256) void vis_weights_kernel(const uint8_t *__restrict__ flags, int n_in,
                                                           int subs, int n_ints, float *__restrict__ w) {
@@ -42,12 +45,12 @@ __global__ __launch_bounds__(256) void vis_weights_kernel(const uint8_t *__restr
     const int64_t P = (int64_t)n_in * (n_in + 1) / 2;
 
     for (int j = blockIdx.y; j < n_ints; j += gridDim.y) {
-        int cnt[4][4] = {};
+        int cnt[2][2] = {};
         for (int w0 = 0; w0 < W; w0 += kWWords) {
             __syncthreads();
             // one wave per input row: 64 lanes read 64 consecutive flags and a
             // ballot of "populated" is two mask words.  A wave owns the rows
-            // r = wave (mod 4) and loads 8 of them before their ballots, so the
+            // r = wave (mod 4) and loads 16 of them before their ballots, so the
             // loads overlap; addresses are clamped into the flag array.
             const int nw = min(kWWords, W - w0);
             const int lane = tid & 63, wave = tid >> 6;
@@ -73,24 +76,24 @@ __global__ __launch_bounds__(256) void vis_weights_kernel(const uint8_t *__restr
             }
             __syncthreads();
             for (int k = 0; k < nw; ++k) {
-                uint32_t a[4], b[4];
+                uint32_t a[2], b[2];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    a[i] = mask[ty * 4 + i][k];
-                    b[i] = mask[kWBlock + tx * 4 + i][k];
+                for (int i = 0; i < 2; ++i) {
+                    a[i] = mask[ty * 2 + i][k];
+                    b[i] = mask[kWBlock + tx * 2 + i][k];
                 }
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < 2; ++i)
 #pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) cnt[i][jj] += __popc(a[i] & b[jj]);
+                    for (int jj = 0; jj < 2; ++jj) cnt[i][jj] += __popc(a[i] & b[jj]);
             }
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int n1 = bi * kWBlock + ty * 4 + i;
+        for (int i = 0; i < 2; ++i) {
+            const int n1 = bi * kWBlock + ty * 2 + i;
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) {
-                const int n2 = bj * kWBlock + tx * 4 + jj;
+            for (int jj = 0; jj < 2; ++jj) {
+                const int n2 = bj * kWBlock + tx * 2 + jj;
                 if (n1 < n_in && n2 <= n1)
                     w[(int64_t)j * P + (int64_t)n1 * (n1 + 1) / 2 + n2] = (float)cnt[i][jj] / (float)subs;
             }

@@ -224,3 +224,11 @@ def test_weights_with_frames_straddling_sub_blocks():
     got = vis.cpu().numpy().astype(np.complex128)
     err = np.linalg.norm(got - want, axis=-1) / np.linalg.norm(want, axis=-1)
     assert err.max() <= 1e-5
+
+
+@pytest.mark.parametrize("n_in", [31, 32, 33, 64, 97])
+def test_vis_weights_at_block_edges(n_in):
+    f = flags_for(n_in, 65, 2, 0.2, seed=n_in)
+    want = oracle.vis_weights(f, 65)
+    g = mwax.vis_weights(torch.from_numpy(f).cuda(), 65).cpu().numpy().astype(np.float64)
+    assert g.shape == want.shape and np.all(np.abs(g - want) <= HALF_ULP * want)
