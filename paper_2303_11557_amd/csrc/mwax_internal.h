@@ -230,7 +230,7 @@ struct XArgs {
                             // non-atomic flush stores instead of adding
     int32_t i32;            // INT8 integrators are int32 pairs (else int64)
 };
-// Segments of a block that one launch works on (FP32 and averaging X-engines):
+// Segments of a block that one launch works on (FP32, small and averaging X-engines):
 // the last, partly filled round of workgroups is then paid once per call.
 constexpr int kXSegs = 8;
 struct XSeg {
@@ -244,8 +244,10 @@ struct XSegList {
     XSeg s[kXSegs];
     int32_t n;
 };
-// FP32 X-engine; a: as launch_xengine but for the fields of the segments.
+// FP32 X-engine, and INT8 / FP16 up to kXSmallInputs inputs; a: as launch_xengine
+// but for the fields of the segments.
 hipError_t launch_xengine_f32(const XArgs &a, const XSegList &segs, hipStream_t s);
+hipError_t launch_xengine_small(int xprec, const XArgs &a, const XSegList &segs, hipStream_t s);
 // Averaging X-engine (plans with mwax_set_averaging): segments of F-channel
 // output channels, accumulated straight into FP64 integrators [N][P][2].
 struct XAvgArgs {
@@ -261,7 +263,7 @@ struct XAvgArgs {
 };
 hipError_t launch_xengine_avg(int xprec, const XAvgArgs &a, hipStream_t s);
 
-// INT8 and FP16.  INT8 launches split every tile's row groups into chunks when
+// INT8 and FP16, more than kXSmallInputs inputs.  INT8 launches split every tile's row groups into chunks when
 // that fills the device's resident workgroup slots more evenly (chunks flush with
 // exact int64 atomic adds); FP16 runs whole segments.
 hipError_t launch_xengine(int xprec, const XArgs &a, hipStream_t s);

@@ -630,11 +630,12 @@ mwax_status mwax_beamform_incoherent(mwax_plan p, int32_t t_avg, int32_t f_avg, 
 mwax_status mwax_correlate(mwax_plan p) {
     if (check_plan(p) != MWAX_OK) return MWAX_E_INVAL;
     if (!p->pending) return fail(MWAX_E_STATE, "no fresh channelised block to correlate");
-    // Averaging and FP32 X-engines: the block's segments (each in a slot of its own)
-    // in launches of up to kXSegs; whole segments, the first one of an integration
-    // stores.
-    if (p->favg > 1 || p->xprec == MWAX_X_FP32) {
-        // a launch holds at most 2^32 - 1 threads, 256 per (segment, channel, tile)
+    // Averaging, FP32 and small-array X-engines: the block's segments (each in a slot
+    // of its own) in launches of up to kXSegs; whole segments, the first one of an
+    // integration stores.
+    if (p->favg > 1 || p->xprec == MWAX_X_FP32 || p->n_in <= kXSmallInputs) {
+        // a launch holds at most 2^32 - 1 threads, 256 per (segment, channel, tile);
+        // the forms with larger workgroups are for far smaller launches
         const int64_t per_seg = (int64_t)xengine_tile_count(p->n_in, kXTileSmall) * (p->L / p->favg) * 256;
         const size_t step = (size_t)std::max<int64_t>(1, std::min<int64_t>(kXSegs, UINT32_MAX / per_seg));
         for (size_t k0 = 0; k0 < p->segs.size(); k0 += step) {
@@ -647,7 +648,11 @@ mwax_status mwax_correlate(mwax_plan p) {
                           s.local0 == 0};
             }
             hipError_t e = timed(p, 1, [&] {
-                if (p->favg == 1) return launch_xengine_f32(xengine_args(p, p->segs[k0]), q, p->stream);
+                if (p->favg == 1) {
+                    const XArgs a = xengine_args(p, p->segs[k0]);
+                    return p->xprec == MWAX_X_FP32 ? launch_xengine_f32(a, q, p->stream)
+                                                   : launch_xengine_small(p->xprec, a, q, p->stream);
+                }
                 XAvgArgs v{};
                 v.chan = p->chan;
                 v.NG = p->NG;

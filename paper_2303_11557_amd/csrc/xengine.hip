@@ -495,7 +495,8 @@ __global__ __launch_bounds__(kThreads, 2) void xengine_mfma(XArgs a) {
 // batch item (four waves) gives the same bits as a plan of its own (eight).
 // Bound by latency.  32 inputs, 128 channels, 10,000 spectra, channelise to emission,
 // 128-edge tiles / this: INT8 123 / 85 us, FP16 279 / 106 us; 64 inputs, 512 channels,
-// 4 x 64 spectra: INT8 189 / 131 us, FP16 115 / 83 us.
+// 4 x 64 spectra in one launch: INT8 189 / 121 us, FP16 115 / 74 us (a launch per
+// segment: 132 and 83 us).
 // ---------------------------------------------------------------------------
 constexpr int kSmallSlices = 8, kSmallG = 8;
 template <int XP>
@@ -630,12 +631,17 @@ __device__ __forceinline__ void small_block(const XArgs &a, int c, int I, int J,
 }
 
 template <int XP, int W>
-__global__ __launch_bounds__(64 * W, 2) void xengine_small(XArgs a) {
+__global__ __launch_bounds__(64 * W, 2) void xengine_small(XArgs a, XSegList segs) {
     __shared__ SmallSum<XP> sum[W > 1 ? 16 : 1][64];
     const int lin = xcd_logical(blockIdx.x, gridDim.x);
-    const int c = lin / a.ntiles;
+    const int cs = lin / a.ntiles, seg = cs / a.L, c = cs - seg * a.L;
+    const XSeg sg = segs.s[seg];
+    a.grp0 = sg.grp0;
+    a.ngrp = sg.ngrp;
+    a.integ = sg.integ;
+    a.first = sg.first;
     int I, J;
-    tile_ij(lin - c * a.ntiles, I, J);
+    tile_ij(lin - cs * a.ntiles, I, J);
     small_block<XP, W>(a, c, I, J, __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), sum);
 }
 
@@ -1313,37 +1319,12 @@ void set_chunks(int xprec, XArgs &a) {
 }  // namespace
 
 bool xengine_accumulates(int xprec, const XArgs &args) {
-    if (args.n_in <= kXSmallInputs) return false;
     XArgs a = args;
     set_chunks(xprec, a);
     return a.nks > 1;
 }
 
-template <int XP>
-static hipError_t launch_xengine_small(const XArgs &args, hipStream_t s) {
-    XArgs a = args;
-    a.ntiles = xengine_tile_count(a.n_in, kXTileTiny);
-    const unsigned blocks = (unsigned)(a.ntiles * a.L);
-    // As many waves as the device holds at two per SIMD, but no more than stages and
-    // no fewer than two (one takes a single stage).  32 tiles FP16, 8,000 spectra x 2,
-    // whole step in us at 8 / 4 / 2 waves: 64 channels 182 / 204 / 263, 128 channels
-    // 360 / 355 / 385, 256 channels 702 / 723 / 685; 512 spectra x 2, 1,024 channels
-    // 359 / 308 / 289.
-    int w = kSmallSlices;
-    while (w > 1 && a.ngrp <= w / 2 * kSmallG) w /= 2;
-    while (w > 2 && (int64_t)blocks * w > 8 * device_cus()) w /= 2;
-    if (w == 1) hipLaunchKernelGGL((xengine_small<XP, 1>), dim3(blocks), dim3(64), 0, s, a);
-    else if (w == 2) hipLaunchKernelGGL((xengine_small<XP, 2>), dim3(blocks), dim3(128), 0, s, a);
-    else if (w == 4) hipLaunchKernelGGL((xengine_small<XP, 4>), dim3(blocks), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((xengine_small<XP, 8>), dim3(blocks), dim3(512), 0, s, a);
-    return hipGetLastError();
-}
-
 hipError_t launch_xengine(int xprec, const XArgs &args, hipStream_t s) {
-    if (args.n_in <= kXSmallInputs && args.ngrp > 0) {
-        if (xprec == MWAX_X_INT8) return launch_xengine_small<MWAX_X_INT8>(args, s);
-        if (xprec == MWAX_X_FP16) return launch_xengine_small<MWAX_X_FP16>(args, s);
-    }
     XArgs a = args;
     set_chunks(xprec, a);
     const int64_t blocks = (int64_t)a.ntiles * a.L * a.nks;
@@ -1359,6 +1340,35 @@ hipError_t launch_xengine(int xprec, const XArgs &args, hipStream_t s) {
             return hipErrorInvalidValue;
     }
     return hipGetLastError();
+}
+
+template <int XP>
+static hipError_t launch_small(const XArgs &args, const XSegList &segs, hipStream_t s) {
+    XArgs a = args;
+    int ngrp = 0;
+    for (int k = 0; k < segs.n; ++k) ngrp = segs.s[k].ngrp > ngrp ? segs.s[k].ngrp : ngrp;
+    a.ntiles = xengine_tile_count(a.n_in, kXTileTiny);
+    const unsigned blocks = (unsigned)(a.ntiles * a.L * segs.n);
+    // As many waves as the device holds at two per SIMD, but no more than stages and
+    // no fewer than two (one takes a single stage).  32 tiles FP16, 8,000 spectra x 2,
+    // whole step in us at 8 / 4 / 2 waves: 64 channels 182 / 204 / 263, 128 channels
+    // 360 / 355 / 385, 256 channels 702 / 723 / 685; 512 spectra x 2, 1,024 channels
+    // 359 / 308 / 289.
+    int w = kSmallSlices;
+    while (w > 1 && ngrp <= w / 2 * kSmallG) w /= 2;
+    while (w > 2 && (int64_t)blocks * w > 8 * device_cus()) w /= 2;
+    if (w == 1) hipLaunchKernelGGL((xengine_small<XP, 1>), dim3(blocks), dim3(64), 0, s, a, segs);
+    else if (w == 2) hipLaunchKernelGGL((xengine_small<XP, 2>), dim3(blocks), dim3(128), 0, s, a, segs);
+    else if (w == 4) hipLaunchKernelGGL((xengine_small<XP, 4>), dim3(blocks), dim3(256), 0, s, a, segs);
+    else hipLaunchKernelGGL((xengine_small<XP, 8>), dim3(blocks), dim3(512), 0, s, a, segs);
+    return hipGetLastError();
+}
+
+hipError_t launch_xengine_small(int xprec, const XArgs &a, const XSegList &segs, hipStream_t s) {
+    if (segs.n < 1 || segs.n > kXSegs || a.n_in > kXSmallInputs) return hipErrorInvalidValue;
+    if (xprec == MWAX_X_INT8) return launch_small<MWAX_X_INT8>(a, segs, s);
+    if (xprec == MWAX_X_FP16) return launch_small<MWAX_X_FP16>(a, segs, s);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_xengine_f32(const XArgs &args, const XSegList &segs, hipStream_t s) {
