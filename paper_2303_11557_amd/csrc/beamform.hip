@@ -67,8 +67,18 @@ __device__ __forceinline__ v16f mma_bf16(const uint4 &a, const uint4 &b, v16f c)
 // on the FP32 instructions, and half their error (2.9e-7 of the rms against
 // 5.7e-7: a sum rounds once per 16 inputs and piece, not once per input and
 // component).  Binary16, 8 to 96 beams: 1.75 to 1.95 times as fast.
+// These instructions take bf16 denormals as zeros, so a weight's pieces and their
+// products with the voltages' (2^-24 at the least) have to be normal: its last bit,
+// 2^-23 of it, at least 2^(24 - 126), the weight at least 2^-79 (kLeastWeight).  And
+// an infinity times another value's piece of zero is a NaN where the whole product
+// is not.  So the beams of a smaller weight, and sums that are not finite, take their
+// values from the whole weights and voltages as in the FP32 plans' kernel.
+constexpr uint32_t kLeastWeight = (127u - 79u) << 23;   // bits of 2^-79
+// (Binary16, more than 32 beams: held to four or, with the doubled tile, three
+// workgroups per CU, which the compiler misses by some registers: 225 / 253 us
+// without, 48 beams of 256 inputs, 128 channels, 2,000 spectra.)
 template <int ES, int WB, int NC>
-__global__ __launch_bounds__(256, 2) void beamform_kernel(BeamArgs a) {
+__global__ __launch_bounds__(256, (ES == 2 && WB == 2 ? 5 - NC : 2)) void beamform_kernel(BeamArgs a) {
     constexpr int G = 16 / ES;
     constexpr int KI = 32 / ES, KB = KI / 16;               // inputs and 16-input blocks per stage
     constexpr int kMT = 32 * NC * (4 / WB), GL = kMT / G;   // spectra and row groups per workgroup
@@ -122,6 +132,7 @@ __global__ __launch_bounds__(256, 2) void beamform_kernel(BeamArgs a) {
             }
         }
     };
+    uint32_t below = 0;   // bit q: the beam of this thread's quad q has a weight below kLeastWeight
     // LDS units of 16 bytes (8 inputs): [block][half][piece][re, im][beam]
     auto store_w = [&](int s, uint8_t *wbuf) {
 #pragma unroll
@@ -130,6 +141,7 @@ __global__ __launch_bounds__(256, 2) void beamform_kernel(BeamArgs a) {
             if (kQuads % 256 != 0 && u >= kQuads) break;
             const int n = s * KI + kq * 4;
             uint8_t *dst = wbuf + (kq / 2 * 6 * 32 * WB + bl) * 16 + (kq & 1) * 8;
+            uint32_t least = 0xffffffffu;   // least nonzero weight: bits, sign dropped, times two, less one
 #pragma unroll
             for (int comp = 0; comp < 2; ++comp) {
                 float v[4];
@@ -137,6 +149,7 @@ __global__ __launch_bounds__(256, 2) void beamform_kernel(BeamArgs a) {
                 for (int e = 0; e < 4; ++e) {
                     const float w = __builtin_canonicalizef(wq[q][2 * e + comp]);   // a quiet NaN keeps its top half
                     v[e] = b0 + bl < a.nb && n + e < a.n_in ? w : 0.0f;
+                    least = min(least, (__float_as_uint(v[e]) << 1) - 1u);
                 }
 #pragma unroll
                 for (int p = 0; p < 3; ++p) {
@@ -146,6 +159,7 @@ __global__ __launch_bounds__(256, 2) void beamform_kernel(BeamArgs a) {
                     for (int e = 0; e < 4; ++e) v[e] = rest_of(v[e]);
                 }
             }
+            below |= least < (kLeastWeight << 1) - 1u ? 1u << q : 0u;
         }
     };
 
@@ -231,6 +245,46 @@ __global__ __launch_bounds__(256, 2) void beamform_kernel(BeamArgs a) {
     for (int s = 0; s < nst; s += 2) {
         iteration(s, xb0, wb0, xb1, wb1);
         iteration(s + 1, xb1, wb1, xb0, wb0);
+    }
+    // sums to form again?  (the LDS of the stages is free now)
+    float z = 0.0f;   // stays zero if every sum is finite
+#pragma unroll
+    for (int nc = 0; nc < NC; ++nc)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z = fmaf(acc_i[nc][r], 0.0f, fmaf(acc_r[nc][r], 0.0f, z));
+    int *flags = reinterpret_cast<int *>(xb0);   // per beam, then per wave
+    const uint64_t found = __ballot(below != 0 || z != 0.0f);
+    if (lane == 0) flags[32 * WB + wave] = found != 0;
+    __syncthreads();
+    const int *any = flags + 32 * WB;
+    if (any[0] | any[1] | any[2] | any[3]) {
+        // on the FP32 instructions, K = (re, im) of one input, straight from global memory
+        if (tid < 32 * WB) flags[tid] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kQ; ++q)
+            if (below >> q & 1u) flags[(tid + q * 256) / (KI / 4)] = 1;
+        __syncthreads();
+        const bool small = flags[wb * 32 + l32] != 0;
+        const float2 *row = wbase + (int64_t)min(wb * 32 + l32, a.nb - 1 - b0) * a.n_in;
+#pragma unroll
+        for (int nc = 0; nc < NC; ++nc) {
+            const int64_t m = m0 + (wm * NC + nc) * 32 + l32;
+            const uint8_t *x0 = base + min(m / G, glast) * gstride;
+            auto odd = [&](float v) { return small || !(fabsf(v) < __builtin_inff()); };
+            v16f er{}, ei{};
+#pragma unroll 1
+            for (int n = 0; n < a.n_in; ++n) {
+                const float2 w = row[n], x = row_value<ES>(x0 + (int64_t)n * kRowBytes, (int)(m % G));
+                er = __builtin_amdgcn_mfma_f32_32x32x2f32(half ? x.y : x.x, half ? -w.y : w.x, er, 0, 0, 0);
+                ei = __builtin_amdgcn_mfma_f32_32x32x2f32(half ? x.y : x.x, half ? w.x : w.y, ei, 0, 0, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                if (odd(acc_r[nc][r])) acc_r[nc][r] = er[r];
+                if (odd(acc_i[nc][r])) acc_i[nc][r] = ei[r];
+            }
+        }
     }
 
     // out[m][c][b]: lane l32 is beam l32 of the wave's block, rows are spectra

@@ -186,3 +186,55 @@ def test_split_weights(prec, n_tiles, L, M, nb, scale):
     hit[:, 0, 0] = True
     assert rel_err(B[~hit], ref[~hit]) < 2e-6
     assert not np.isfinite(Binf[hit]).any() and np.array_equal(Binf[~hit], B[~hit].astype(np.complex64))
+
+
+@pytest.mark.parametrize("prec", ["fp16", "int8"])
+@pytest.mark.parametrize("scale", [2.0 ** -130, 2.0 ** -112, 2.0 ** -81])
+def test_small_weights(prec, scale):
+    """Weights whose lower bf16 pieces, or their products, are no normal numbers:
+    the same bound as all others (the beams themselves are normal: at the smallest
+    scale the sums of 34 products of 30 and more are above 2^-124)."""
+    n_tiles, L, M, nb = 17, 2, 70, 33
+    n = 2 * n_tiles
+    rng = np.random.default_rng(int(-np.log2(scale)))
+    if prec == "int8":
+        x, post = rng.integers(-127, 128, size=(M, L, n, 2)).astype(np.int8), 1.0
+    else:
+        x, post = (rng.normal(size=(M, L, n, 2)) * 30.0).astype(np.float16), 2.0
+    w = ((rng.normal(size=(L, nb, n)) + 1j * rng.normal(size=(L, nb, n))) * scale).astype(np.complex64)
+    with Plan(make_config(n_tiles, L=L, T=M, xprec=prec, max_samples=L * M)) as p:
+        p.load_channelised(torch.from_numpy(x).cuda())
+        B = p.beamform(torch.from_numpy(w).cuda()).cpu().numpy().astype(np.complex128)
+    ref = oracle.beamform((x[..., 0].astype(np.float64) + 1j * x[..., 1]) * post, w.astype(np.complex128) / scale)
+    assert rel_err(B / scale, ref) < 2e-6
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp16", "int8"])
+def test_infinite_values(prec):
+    """An infinite voltage or weight makes the sums it is part of infinite (or NaN where
+    FP32 products say so: infinity times zero, infinity less infinity), and no others,
+    also in the last input of a ragged stage and through weights of few bits."""
+    n_tiles, L, M, nb = 17, 2, 40, 3
+    n = 2 * n_tiles
+    x = np.ones((M, L, n, 2), {"int8": np.int8, "fp16": np.float16, "fp32": np.float32}[prec])
+    w = np.full((L, nb, n), 1.0 + 0.5j, np.complex64)
+    w[:, 1] = 0.7 + 0.3j
+    w[:, 2] = 1.0
+    if prec != "int8":
+        x[3, 1, 5, 0] = np.inf
+        x[4, 1, n - 1, 1] = -np.inf
+    w[0, 0, 7] = complex(np.inf, 1.0)
+    with Plan(make_config(n_tiles, L=L, T=M, xprec=prec, max_samples=L * M)) as p:
+        p.load_channelised(torch.from_numpy(x).cuda())
+        B = p.beamform(torch.from_numpy(w).cuda()).cpu().numpy()
+    X, W = x.astype(np.float64)[:, :, None], w.astype(np.complex128)[None]
+    post = 2.0 if prec == "fp16" else 1.0
+    with np.errstate(invalid="ignore"):
+        re = (W.real * X[..., 0] - W.imag * X[..., 1]).sum(-1) * post
+        im = (W.real * X[..., 1] + W.imag * X[..., 0]).sum(-1) * post
+    for got, want in ((B.real, re), (B.imag, im)):
+        fin = np.isfinite(want)
+        assert np.array_equal(np.isnan(got), np.isnan(want))
+        assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+        assert np.allclose(got[fin], want[fin], rtol=2e-6)
+    assert not np.isfinite(re).all() and np.isfinite(re).sum() > re.size // 3
