@@ -815,7 +815,7 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
     const int fb_off = (tb.sb >> 1) * kPanel + (tb.sb & 1) * kBlock + half * 512 + l32 * 16;
     constexpr uint32_t kFlip = INT8 ? 0xffffffffu : 0x80008000u;
 
-    // FIRST: the channel's first stage starts its partial sums (no cleared registers)
+    // FIRST: the stage starts new partial sums (no cleared registers)
     auto compute = [&](const uint8_t *st, auto first_c) {
         constexpr bool FIRST = decltype(first_c)::value;
         uint4 fa[2], fb[2];
@@ -854,8 +854,11 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
         }
     };
     load_window(0);
-    // compute cursor: channel index and the stage within the channel
-    int cm_ci = 0, cm_ls = 0;
+    // compute cursor: channel index, the stage within the stages after which its partial
+    // sums are taken (all of the channel's, or kTake: INT8 partials are int32, see
+    // MfmaT), their number and that of the channel's stages that follow them
+    constexpr int kTake = T::kFlushGroups / kXG;
+    int cm_ci = 0, cm_ls = 0, cm_len = min(spc, kTake), cm_rest = spc - cm_len;
     auto iteration = [&](int s, auto b_c) {
         constexpr int B = decltype(b_c)::value;
         copy_next(bufs[(B + kAvgDist) % kNBuf]);
@@ -864,7 +867,7 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
                 if (cm_ls == 0) compute(bufs[B], std::true_type{});
                 else compute(bufs[B], std::false_type{});
             }
-            if (++cm_ls == spc) {
+            if (++cm_ls == cm_len) {
                 // the channel's partials, scaled and weighted, into the sums
                 if (active) {
                     const int t = (cm_ci >> 6) & 3;
@@ -877,7 +880,12 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
                     }
                 }
                 cm_ls = 0;
-                if ((++cm_ci & 255) == 0 && cm_ci < nch) load_window(cm_ci);
+                if (cm_rest == 0) {
+                    cm_rest = spc;
+                    if ((++cm_ci & 255) == 0 && cm_ci < nch) load_window(cm_ci);
+                }
+                cm_len = min(cm_rest, kTake);
+                cm_rest -= cm_len;
             }
         }
         stage_barrier<TE, kAvgDist>();

@@ -319,3 +319,22 @@ def test_x_engine_averaging_tile_order_and_errors():
         with pytest.raises(mwax.MwaxError) as e:
             p.set_averaging(F)
         assert e.value.status == mwax.MWAX_E_UNSUPPORTED
+
+
+@pytest.mark.parametrize("prec,v", [("int8", 127), ("fp16", 1)])
+def test_x_engine_averaging_long_segments(prec, v):
+    # one segment of more spectra than the 32-bit partial sums of full-scale int8
+    # codes can hold (66,571): they are taken into the sums before.  256 output
+    # channels: the 64-edge kernel.  x_1 conj(x_0) = (v - v i)^2 = -2 v^2 i
+    Lc, F, T = 512, 2, 70000
+    x = torch.full((T, Lc, 2, 2), v, dtype=torch.int8 if prec == "int8" else torch.float16, device="cuda")
+    x[:, :, 1, 1] = -v
+    with Plan(make_config(1, L=Lc, T=T, xprec=prec, max_samples=Lc * T)) as p:
+        p.set_averaging(F)
+        p.load_channelised(x)
+        p.correlate()
+        got = p.integrate(1).cpu().numpy()[0].astype(np.complex128)
+    post = 1.0 if prec == "int8" else 2.0 ** (2 * ((int(math.log2(Lc)) + 1) // 2))
+    want = 2.0 * v * v * T * post * np.array([1, -1j, 1])
+    assert got.shape == (Lc // F, 3)
+    assert np.all(np.abs(got - want) <= (F + 3) * 2.0 ** -24 * np.abs(want))   # takes, sums and emission
