@@ -332,8 +332,6 @@ struct PackArgs {
     float *scales_out;      // raw mode: copy of s_c, may be NULL
     int32_t order;          // mwax_order; 2 = raw int64; 3 = averaged by F (CHAN_TRI)
     int32_t clear;          // zero the integrators after reading them
-    int32_t fix_im;         // FP64 integrators of INT8 codes (averaging X-engine): subtract
-                            // the row's auto from the imaginary parts
     int32_t i32;            // INT8 integrators are int32 pairs (else int64)
     int32_t L;
     int32_t n_in;

@@ -14,10 +14,9 @@
 // INT8 integrators hold Im V[n1,n2] - sum_m re_n1[m] (the X-engine forms its
 // imaginary operand from one's complements); the autos, whose imaginary parts
 // are zero, therefore hold -sum_m re_n1[m], and every entry of row n1 is
-// corrected by subtracting its auto's imaginary part: exactly, in integers, or
-// for INT8 plans that average in their X-engine in FP64, where the same sums are
-// scaled and weighted over the channels.  Slots are cleared (where they have to
-// be) by a separate fill after the pack, never while it reads them.
+// corrected exactly by subtracting its auto's imaginary part.  Slots are cleared
+// (where they have to be) by a separate fill after the pack, never while it reads
+// them.
 #include <algorithm>
 
 #include "mwax_internal.h"
@@ -33,9 +32,8 @@ __device__ __forceinline__ int64_t tri_row(int64_t t) {
 }
 
 // What the integrators hold.
-enum Source { kI32, kI64, kF64, kF64Fix };   // kF64Fix: the row's auto is subtracted from the imaginary parts
+enum Source { kI32, kI64, kF64 };
 constexpr bool is_int(int S) { return S == kI32 || S == kI64; }
-constexpr bool needs_auto(int S) { return S != kF64; }
 
 // Entry p of the channel whose integrators start at base (elements of the
 // source); d: the auto of p's row (sources that need it).
@@ -51,10 +49,7 @@ __device__ __forceinline__ auto entry(const void *base, int64_t p, int64_t d) {
         x.y -= v[d].y;
         return x;
     } else {
-        const double2 *v = reinterpret_cast<const double2 *>(base);
-        double2 x = v[p];
-        if constexpr (S == kF64Fix) x.y -= v[d].y;
-        return x;
+        return reinterpret_cast<const double2 *>(base)[p];
     }
 }
 template <int S>
@@ -85,7 +80,7 @@ __global__ __launch_bounds__(256) void pack_tri_kernel(PackArgs a, int per_threa
     const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const int c0 = blockIdx.y * per_thread, c1 = min(a.L, c0 + per_thread);
     if (p < a.P) {
-        const int64_t d = needs_auto(S) ? auto_of(tri_row(p)) : 0;
+        const int64_t d = is_int(S) ? auto_of(tri_row(p)) : 0;
 #pragma unroll 4
         for (int c = c0; c < c1; ++c) {
             if constexpr (RAW) {
@@ -113,7 +108,7 @@ __global__ __launch_bounds__(256) void pack_avg_kernel(PackArgs a) {
     const bool even = (a.F & 1) == 0, centre = a.F > 1 && o == oc;
     const int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (p >= a.P) return;
-    const int64_t d = needs_auto(S) ? auto_of(tri_row(p)) : 0;
+    const int64_t d = is_int(S) ? auto_of(tri_row(p)) : 0;
     double re = 0.0, im = 0.0, wsum = 0.0;
     int c = ((a.L / 2 + (o - oc) * a.F - half) % a.L + a.L) % a.L;
     auto add = [&](double w) {
@@ -250,7 +245,7 @@ static hipError_t launch_pack_source(const PackArgs &a, hipStream_t s) {
 
 hipError_t launch_pack(const PackArgs &a, hipStream_t s) {
     hipError_t e = a.is_int ? (a.i32 ? launch_pack_source<kI32>(a, s) : launch_pack_source<kI64>(a, s))
-                            : (a.fix_im ? launch_pack_source<kF64Fix>(a, s) : launch_pack_source<kF64>(a, s));
+                            : launch_pack_source<kF64>(a, s);
     if (e != hipSuccess || !a.clear) return e;
     return launch_fill_zero(a.integ, clear_bytes(a), s);
 }

@@ -708,7 +708,6 @@ static mwax_status emit(mwax_plan p, void *d_vis, float *d_scales, int32_t max_i
         a.scales_out = d_scales ? d_scales + (size_t)n * p->L : nullptr;
         a.order = order;
         a.clear = p->clear_on_emit && !pre;
-        a.fix_im = pre && p->xprec == MWAX_X_INT8;
         a.i32 = p->integ32;
         a.L = pre ? p->L / p->favg : p->L;
         a.n_in = p->n_in;

@@ -110,6 +110,11 @@ __device__ __forceinline__ int xcd_logical(int b, int nb) {
     return (b & 7) * (full >> 3) + (b >> 3);
 }
 
+// Negation of four int8 values in [-127, 127].
+__device__ __forceinline__ uint32_t neg_i8x4(uint32_t x) {
+    return (0x80808080u - (x & 0x7f7f7f7fu)) ^ (~x & 0x80808080u);
+}
+
 template <int XP>
 struct MfmaT;
 template <>
@@ -137,6 +142,15 @@ struct MfmaT<MWAX_X_FP16> {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(av, bv, c, 0, 0, 0);
     }
 };
+
+// The B operand of Im V (see the file comment) from that of Re V.  INT8: EXACT or by
+// one's complements (see below).
+template <int XP, bool EXACT>
+__device__ __forceinline__ uint4 im_operand(uint4 v) {
+    if constexpr (XP == MWAX_X_FP16) return make_uint4(v.z ^ 0x80008000u, v.w ^ 0x80008000u, v.x, v.y);
+    else if constexpr (EXACT) return make_uint4(neg_i8x4(v.z), neg_i8x4(v.w), v.x, v.y);
+    else return make_uint4(~v.z, ~v.w, v.x, v.y);
+}
 
 // One workgroup = one channel x four 64 x 64 blocks of the lower triangle (see
 // TriBlock; off the diagonal a 128 x 128 tile), one per wave in 2 x 2 parts of
@@ -262,7 +276,6 @@ __device__ __forceinline__ void xengine_tile_loop(const XArgs &a, const XLds &ld
     // `half` of its row l32
     const int fa_off = GEO::slot(tb.sa) + half * 512 + l32 * 16;
     const int fb_off = GEO::slot(tb.sb) + half * 512 + l32 * 16;
-    constexpr uint32_t kFlip = INT8 ? 0xffffffffu : 0x80008000u;
 
     // One stage of matrix-core work from one buffer; the fragments of row group
     // k+1 are read while the MFMAs of group k run.
@@ -283,10 +296,7 @@ __device__ __forceinline__ void xengine_tile_loop(const XArgs &a, const XLds &ld
             const int sl = k & 1;
             uint4 fb2[MB];
 #pragma unroll
-            for (int m = 0; m < MB; ++m) {
-                const uint4 v = fb[sl][m];
-                fb2[m] = make_uint4(v.z ^ kFlip, v.w ^ kFlip, v.x, v.y);
-            }
+            for (int m = 0; m < MB; ++m) fb2[m] = im_operand<XP, false>(fb[sl][m]);
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
@@ -520,17 +530,16 @@ struct SmallStage {
             b[k] = *reinterpret_cast<const uint4 *>(pb + o);
         }
     }
-    template <int XP>
+    template <int XP, bool EXACT>
     __device__ __forceinline__ void multiply(int g0, int gend, typename MfmaT<XP>::acc_t &re,
                                              typename MfmaT<XP>::acc_t &im) const {
-        constexpr uint32_t kFlip = XP == MWAX_X_INT8 ? 0xffffffffu : 0x80008000u;
         const uint4 zero = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
         for (int k = 0; k < kSmallG; ++k) {
             const bool in = g0 + k < gend;
             const uint4 x = in ? a[k] : zero, y = in ? b[k] : zero;
             re = MfmaT<XP>::mma(x, y, re);
-            im = MfmaT<XP>::mma(x, make_uint4(y.z ^ kFlip, y.w ^ kFlip, y.x, y.y), im);
+            im = MfmaT<XP>::mma(x, im_operand<XP, EXACT>(y), im);
         }
     }
 };
@@ -576,7 +585,7 @@ __device__ __forceinline__ void small_block(const XArgs &a, int c, int I, int J,
         acc_t re{}, im{};
         SmallStage st;
         st.fetch(pa, pb, gstride, 0, a.ngrp);
-        st.template multiply<XP>(0, a.ngrp, re, im);
+        st.template multiply<XP, false>(0, a.ngrp, re, im);
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
             Sum v;
@@ -609,7 +618,7 @@ __device__ __forceinline__ void small_block(const XArgs &a, int c, int I, int J,
         for (int s = slice; s < nst; s += kSmallSlices) {
             const SmallStage cur = next;
             if (s + kSmallSlices < nst) next.fetch(pa, pb, gstride, (s + kSmallSlices) * kSmallG, a.ngrp);
-            cur.template multiply<XP>(s * kSmallG, a.ngrp, re, im);
+            cur.template multiply<XP, false>(s * kSmallG, a.ngrp, re, im);
             groups += kSmallG;
             if (groups == T::kFlushGroups) {
                 collect();
@@ -716,15 +725,15 @@ __global__ __launch_bounds__(kThreads, 2) void xengine_batch(XBatchArgs b) {
 // integration, stored) once into FP64 integrators [N][P].  The fine-channel
 // integrators are never written: per 250 ms integration at 256 tiles and
 // L = 6400 that is 6.7 GB of flushes and 6.7 GB of pack reads avoided.
-// The INT8 Im operand is the one's complement of the per-channel kernel: each
-// channel's imaginary partials lack sum_m re_n1[m], and so, scaled and weighted
-// alike, do the sums; the pack step subtracts the autos' sums, which hold just
-// that.  Bound by the copies from L2 into LDS: 512 inputs at 40 kHz read every row
-// nine times, 15 GB per four 250 ms integrations, 12 TB/s at 1.25 ms (the copies
-// of the per-channel kernel reach no more alone); the VALU's conversion and
-// weighted addition of every partial comes next.  1.42 ms with the exact negation,
-// cleared partials and an idle wave on every diagonal tile; 1.74 ms with a launch
-// per integration.
+// The INT8 Im operand is the exact negation (-im, re), not the one's complement of
+// the per-channel kernel: the sums are FP32 here, and with sum_m re_n1[m] in them
+// would take its rounding too, which is many times theirs where an input has a large
+// mean (the one's complement takes 2 % less at 512 inputs).  Bound by the copies from
+// L2 into LDS: 512 inputs at 40 kHz read every row nine times, 15 GB per four 250 ms
+// integrations, 12 TB/s at 1.28 ms (the copies of the per-channel kernel reach no more
+// alone); the VALU's conversion and weighted addition of every partial comes next.
+// 1.40 ms with cleared partials and an idle wave on every diagonal tile; 1.74 ms with
+// a launch per integration.
 // ---------------------------------------------------------------------------
 // Copies run three stages ahead here (two in the per-channel kernel): a work
 // item's stages are short (4 MFMAs per wave at 250 ms integrations) and every
@@ -739,7 +748,6 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
     constexpr int kGroupPitch = GEO::kGroupPitch, kPanel = GEO::kPanel;
     using T = MfmaT<XP>;
     using acc_t = typename T::acc_t;
-    constexpr bool INT8 = XP == MWAX_X_INT8;
     __shared__ __align__(16) uint8_t lds0[GEO::kStage], lds1[GEO::kStage], lds2[GEO::kStage], lds3[GEO::kStage];
     uint8_t *const bufs[4] = {lds0, lds1, lds2, lds3};
     static_assert(kNBuf == 4, "four stage buffers");
@@ -813,7 +821,6 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
     for (int r = 0; r < 16; ++r) sr[r] = si[r] = 0.0f;
     const int fa_off = (tb.sa >> 1) * kPanel + (tb.sa & 1) * kBlock + half * 512 + l32 * 16;
     const int fb_off = (tb.sb >> 1) * kPanel + (tb.sb & 1) * kBlock + half * 512 + l32 * 16;
-    constexpr uint32_t kFlip = INT8 ? 0xffffffffu : 0x80008000u;
 
     // FIRST: the stage starts new partial sums (no cleared registers)
     auto compute = [&](const uint8_t *st, auto first_c) {
@@ -828,7 +835,7 @@ __global__ __launch_bounds__(kThreads, 4) void xengine_avg(XAvgArgs a) {
                 fb[(k + 1) & 1] = *reinterpret_cast<const uint4 *>(st + (k + 1) * kGroupPitch + fb_off);
             }
             const uint4 v = fb[k & 1];
-            const uint4 fb2 = make_uint4(v.z ^ kFlip, v.w ^ kFlip, v.x, v.y);
+            const uint4 fb2 = im_operand<XP, true>(v);
             re = T::mma(fa[k & 1], v, FIRST && k == 0 ? acc_t{} : re);
             im = T::mma(fa[k & 1], fb2, FIRST && k == 0 ? acc_t{} : im);
         }
@@ -965,7 +972,7 @@ __global__ __launch_bounds__(64 * kSmallSlices, 2) void xengine_avg_small(XAvgAr
         for (int g = g0; g < g1; g += kSmallG) {
             const SmallStage cur = next;
             if (g + kSmallG < g1) next.fetch(base + rowA, base + rowB, gstride, g + kSmallG, g1);
-            cur.template multiply<XP>(g, g1, re, im);
+            cur.template multiply<XP, true>(g, g1, re, im);
         }
 #pragma unroll
         for (int r = 0; r < 16; ++r) {

@@ -338,3 +338,23 @@ def test_x_engine_averaging_long_segments(prec, v):
     want = 2.0 * v * v * T * post * np.array([1, -1j, 1])
     assert got.shape == (Lc // F, 3)
     assert np.all(np.abs(got - want) <= (F + 3) * 2.0 ** -24 * np.abs(want))   # takes, sums and emission
+
+
+def test_x_engine_averaging_keeps_small_imaginary_parts():
+    # a constant real input against one of mean zero: the products' sums are small
+    # next to the sum of the constant, and exact in FP32 with the weights of F = 4
+    # (but for the centre channel's thirds), so they are emitted exactly
+    Lc, F, T, ints = 256, 4, 20000, 4          # 64 output channels x 4 segments: the 64-edge kernel
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.randint(-1, 2, (ints * T, Lc, 2, 2), generator=g, dtype=torch.int8, device="cuda")
+    x[:, :, 1, 0] = 127
+    x[:, :, 1, 1] = 0
+    s = x[:, :, 0].reshape(ints, T, Lc, 2).sum(1, dtype=torch.int64).cpu().numpy().astype(np.float64)
+    with Plan(make_config(1, L=Lc, T=T, xprec="int8", max_samples=Lc * T * ints)) as p:
+        p.set_averaging(F)
+        p.load_channelised(x)
+        p.correlate()
+        got = p.integrate(ints).cpu().numpy()[:, :, 1]
+    want = oracle.fscrunch(127.0 * (s[..., :1] - 1j * s[..., 1:]), F)[..., 0]
+    rest = np.arange(Lc // F) != Lc // F // 2
+    assert np.array_equal(got[:, rest], want[:, rest].astype(np.complex64))
