@@ -93,6 +93,7 @@ constexpr int cp_pad(int L, int XP) {
 // Each group transforms FPG consecutive frames of one input, so that the
 // results of FPG frames leave in one packed LDS write; the workgroup covers
 // R inputs x G frames (one 32-byte row group per channel and input).
+constexpr int64_t kLeast = 2048;   // workgroups that fill the device (about all that can be resident)
 template <int L, int XP>
 struct FCfg {
     using SH = FftShape<L, XP>;
@@ -159,6 +160,15 @@ struct FCfg {
     // share output lines) drift apart.  Measured at 256 tiles, 8 s: 65,536 at every
     // length but 256, where 131,072 is 10 % faster (32,768 - 262,144 swept).
     static constexpr int64_t GRID_CAP = L == 256 ? 131072 : 65536;
+    // most rounds of a single-plan launch (main_grid): eight, but FP32 at L >= 512, whose
+    // items write 64 or 32 bytes of a channel's 128-byte lines, loses more by the drift
+    // than the set-up costs: at L = 512 two, at L = 1024 one once three do not hold the
+    // launch to kLeast.  us in eight rounds / these: L = 512, 128 inputs x 400 spectra
+    // 90 / 82, 512 x 400 340 / 307; L = 1024, 128 x 520 317 / 269, 256 x 1,200 1,509 /
+    // 1,192 (64 x 320: 71 in three, 90 in one).
+    static constexpr int64_t most_rounds(int64_t items) {
+        return XP != MWAX_X_FP32 || L < 512 ? 8 : (L == 512 ? 2 : (items <= 3 * kLeast ? 3 : 1));
+    }
 };
 
 // One complex int8 sample, converted exactly.  Written with arithmetic shifts of
@@ -726,16 +736,18 @@ constexpr int cfg_value_lds(bool stats) {
 }
 
 // Workgroups of a single-plan launch over `items` items: whole rounds (a last round
-// of a few items costs as much as a full one), about eight of them, so that each
-// workgroup's set-up (twiddles, scales) is spread over several items, with no fewer
-// than 2,048 workgroups (all that can be resident) and no more than cap.  Rounds of
-// the 8 XCDs.  256 tiles, 1 s INT8 at L = 128 / 256: 881, 983 -> 720, 809 us with
-// 65,536 workgroups (2.4 rounds) before; 64 tiles: 242 -> 175; 128 tiles at L = 512
-// / 1024: 564, 580 -> 482, 502; 256 tiles, 8 s: 19.5 -> 20 rounds, 5.59 -> 5.41 ms.
-int main_grid(int64_t items, int64_t cap) {
-    constexpr int64_t kRounds = 8, kLeast = 2048;
+// of a few items costs as much as a full one), so that each workgroup's set-up
+// (twiddles, scales) is spread over several items, and no more than cap.  As many
+// rounds as bring the launch to kLeast workgroups or fewer, but no more than `most`,
+// with which large launches have more workgroups.
+// Rounds of the 8 XCDs.  256
+// tiles, 1 s INT8 at L = 128 / 256: 881, 983 -> 720, 809 us with 65,536 workgroups
+// (2.4 rounds) before; 64 tiles: 242 -> 175; 128 tiles at L = 512 / 1024: 564, 580 ->
+// 482, 502; 256 tiles, 8 s: 19.5 -> 20 rounds, 5.59 -> 5.41 ms.
+int main_grid(int64_t items, int64_t cap, int64_t most) {
     if (items <= kLeast) return (int)items;
-    const int64_t rounds = std::max((items + cap - 1) / cap, std::min(kRounds, (items + kLeast - 1) / kLeast));
+    const int64_t fill = (items + kLeast - 1) / kLeast;
+    const int64_t rounds = std::max((items + cap - 1) / cap, std::min(most, fill));
     return (int)(((items + rounds - 1) / rounds + 7) / 8 * 8);
 }
 
@@ -746,7 +758,10 @@ hipError_t launch_L(const FArgs &a, hipStream_t s) {
     if (a.R != C::R) return hipErrorInvalidValue;
     const int lds = fengine_lds_bytes(L, XP, a.R, stats);
     int grid = fengine_grid(a.n_in, a.R, a.ngrp, stats);
-    if (!stats) grid = main_grid((int64_t)a.ngrp * ((a.n_in + C::R - 1) / C::R), C::GRID_CAP);
+    if (!stats) {
+        const int64_t items = (int64_t)a.ngrp * ((a.n_in + C::R - 1) / C::R);
+        grid = main_grid(items, C::GRID_CAP, C::most_rounds(items));
+    }
     if (grid < 1) return hipSuccess;
     // allow dynamic LDS beyond the default limit (once per instantiation)
     const int variant = stats ? 1 : (a.dl ? 2 : 0);
