@@ -740,13 +740,15 @@ constexpr int cfg_value_lds(bool stats) {
 // (twiddles, scales) is spread over several items, and no more than cap.  As many
 // rounds as bring the launch to kLeast workgroups or fewer, but no more than `most`,
 // with which large launches have more workgroups.
-// Rounds of the 8 XCDs.  256
+// Up to an eighth past kLeast a round of one item each is the faster: 64 inputs,
+// 2,112 items, INT8, L = 512 / 1024: 40.0, 69.4 us in two rounds, 38.5, 66.6 in one
+// (2,560 items: 41.2, 71.5 in two, 42.8, 74.8 in one).  Rounds of the 8 XCDs.  256
 // tiles, 1 s INT8 at L = 128 / 256: 881, 983 -> 720, 809 us with 65,536 workgroups
 // (2.4 rounds) before; 64 tiles: 242 -> 175; 128 tiles at L = 512 / 1024: 564, 580 ->
 // 482, 502; 256 tiles, 8 s: 19.5 -> 20 rounds, 5.59 -> 5.41 ms.
 int main_grid(int64_t items, int64_t cap, int64_t most) {
     if (items <= kLeast) return (int)items;
-    const int64_t fill = (items + kLeast - 1) / kLeast;
+    const int64_t fill = items < kLeast / 8 * 9 ? 1 : (items + kLeast - 1) / kLeast;
     const int64_t rounds = std::max((items + cap - 1) / cap, std::min(most, fill));
     return (int)(((items + rounds - 1) / rounds + 7) / 8 * 8);
 }
