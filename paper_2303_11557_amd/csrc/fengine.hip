@@ -77,6 +77,15 @@ __device__ __forceinline__ float2 delay_gain(int ks, float alpha, float phi) {
     sincospif(-2.0f * fmaf((float)ks, alpha, phi), &sn, &cs);
     return make_float2(cs, sn);
 }
+// exp(-2 pi i x), and the product of two of these, in FP64.
+__device__ __forceinline__ double2 turn(double x) {
+    double sn, cs;
+    sincospi(-2.0 * x, &sn, &cs);
+    return make_double2(cs, sn);
+}
+__device__ __forceinline__ double2 turn_by(double2 a, double2 b) {
+    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
 
 constexpr int kThreads = 256;   // default workgroup size (see FCfg::THREADS)
 
@@ -364,6 +373,36 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
         }
         for (int t = 0; t < FPG; ++t) {
             const int f = pk * FPG + t;
+            // this frame's delay (signal path n0 + nl) and phase offset
+            float dl_alpha = 0.0f, dl_phi = 0.0f;
+            // CHAIN (binary16): a lane's bins of a column are evenly spaced, so its
+            // gains turn by the same angle from one to the next: in FP64, whose roundings
+            // do not reach FP32, two sincos per column and four multiply-adds per bin
+            // instead of a sincos per bin (that of a bin in FP32 is off by 6e-8 rms, for
+            // delays of many samples by more; these by the one rounding to FP32).  Formed
+            // before the frame is loaded, when registers are free.  186 inputs, 1 s at L =
+            // 256 / 1024: 461, 697 us; with a sincos per bin and two workgroups per CU
+            // 752, 1,227.  INT8 and FP32 plans evaluate every bin.
+            constexpr bool CHAIN = DELAY && XP == MWAX_X_FP16 && L2 > 1;
+            constexpr int NT = P > 1 || L2 == 1 ? L1 : L2, NC = L1 / NT;   // bins of a column, columns
+            double2 first[CHAIN ? NC : 1], by;
+            if constexpr (DELAY) {
+                float d = 0.0f;
+                if (nl < nrows && f < fvalid)
+                    d = a.dl[(int64_t)(n0 + nl) * a.dl_ld + (a.dl_f0 + lf0 + f) / a.dl_fps];
+                const double ph = (double)d * a.dl_nu;
+                dl_phi = (float)(ph - rint(ph));
+                dl_alpha = d * (1.0f / (float)L);
+                if constexpr (CHAIN) {
+                    // column u: bins k0 + L / NT t; t >= NT / 2 are the negative
+                    // frequencies t - NT: from -NT / 2 on
+#pragma unroll
+                    for (int u = 0; u < NC; ++u)
+                        first[u] = turn((bin_of<L, XP>(r, u * NT) - L / 2) * ((double)d / L) + (ph - rint(ph)));
+                    by = turn((double)d / NT);
+                }
+            }
+
             float2 v[L1];
             if constexpr (C::DIRECT) {
 #pragma unroll
@@ -415,55 +454,12 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
             }
             dft_regs<L1>(v);
 
-            // this frame's delay (signal path n0 + nl) and phase offset
-            float dl_alpha = 0.0f, dl_phi = 0.0f;
-            // CHAIN (binary16): a lane's bins of a column are evenly spaced, so its
-            // gains are a base times powers of the step between them: two sincos and
-            // a few products per frame instead of a sincos per bin.  The gains differ
-            // from the direct ones by at most a few 2^-24, a thousandth of the
-            // binary16 rounding that follows; INT8 and FP32, whose results would show
-            // it, evaluate every bin.  186 inputs, 1 s at L = 1024 with delays: 1330
-            // -> 875 us (with the third workgroup of SPLIT's comment).
-            constexpr bool CHAIN = DELAY && XP == MWAX_X_FP16 && L2 > 1;
-            constexpr int NT = P > 1 ? L1 : L2;          // bins of a column, evenly spaced
-            float2 pw[CHAIN ? NT / 2 + 1 : 1], gb[CHAIN && P == 1 ? U : 1];
-            if constexpr (DELAY) {
-                float d = 0.0f;
-                if (nl < nrows && f < fvalid)
-                    d = a.dl[(int64_t)(n0 + nl) * a.dl_ld + (a.dl_f0 + lf0 + f) / a.dl_fps];
-                const double ph = (double)d * a.dl_nu;
-                dl_phi = (float)(ph - rint(ph));
-                dl_alpha = d * (1.0f / (float)L);
-            }
-            auto make_gains = [&] {   // just before they are used: they live with the spectrum only
-                if constexpr (CHAIN) {
-#pragma unroll
-                for (int u = 0; u < (P == 1 ? U : 1); ++u)
-                    gb[u] = delay_gain(P > 1 ? bin_of<L, XP>(r, 0) : r * U + u, dl_alpha, dl_phi);
-                pw[0] = make_float2(1.0f, 0.0f);
-                pw[1] = delay_gain(L / NT, dl_alpha, 0.0f);
-#pragma unroll
-                for (int t = 2; t <= NT / 2; ++t) {   // products of the two halves of t: few roundings
-                    const float2 x = pw[t / 2], y = pw[t - t / 2];
-                    pw[t] = make_float2(x.x * y.x - x.y * y.y, x.x * y.y + x.y * y.x);
-                }
-                }
-            };
-
-            // consume output slot i (FFT bin of this lane) with value X; tc: the
-            // frame's place in its pack as a compile-time constant (see emit_frame)
-            auto emit = [&](int i, float2 X, auto tc) {
+            // consume output slot i (FFT bin of this lane) with value X and, if CHAIN, gain
+            // g; tc: the frame's place in its pack as a compile-time constant (see emit_frame)
+            auto emit = [&](int i, float2 X, float2 g, auto tc) {
                 constexpr int T = decltype(tc)::value;
                 if constexpr (DELAY) {
-                    float2 g;
-                    if constexpr (CHAIN) {
-                        // slot i is bin t of its column; the upper half are the negative
-                        // frequencies t - NT, conjugate powers
-                        const int t = P > 1 ? i / P + L1 / P * (i % P) : i % L2;
-                        const float2 w = t < NT / 2 ? pw[t] : make_float2(pw[NT - t].x, -pw[NT - t].y);
-                        const float2 c = gb[P > 1 ? 0 : i / L2];
-                        g = make_float2(c.x * w.x - c.y * w.y, c.x * w.y + c.y * w.x);
-                    } else {
+                    if constexpr (!CHAIN) {
                         const int k = bin_of<L, XP>(r, i);
                         g = delay_gain(k < L / 2 ? k : k - L, dl_alpha, dl_phi);
                     }
@@ -528,11 +524,25 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
                 else body(std::integral_constant<int, 1>{});
             };
 
-            if constexpr (L2 == 1) {
-                emit_frame([&](auto tc) {
+            // emit the column of slots i0 .. i0 + NT - 1 with values w
+            auto emit_column = [&](int i0, const float2 *w, auto tc) {
+                if constexpr (CHAIN) {
+                    double2 g = first[i0 / NT];
 #pragma unroll
-                    for (int k = 0; k < L1; ++k) emit(k, v[k], tc);
-                });
+                    for (int e = 0; e < NT; ++e) {
+                        const int t = (e + NT / 2) % NT;
+                        const int i = P > 1 ? t % (L1 / P) * P + t / (L1 / P) : t;
+                        emit(i0 + i, w[i], make_float2((float)g.x, (float)g.y), tc);
+                        if (e + 1 < NT) g = turn_by(g, by);
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < NT; ++i) emit(i0 + i, w[i], float2{}, tc);
+                }
+            };
+
+            if constexpr (L2 == 1) {
+                emit_frame([&](auto tc) { emit_column(0, v, tc); });
             } else {
 #pragma unroll
                 for (int k1 = 1; k1 < L1; ++k1) {      // W_L^0 = 1
@@ -607,11 +617,7 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
                             dft_regs<P>(w + j * P);
                         }
                     }
-                    make_gains();
-                    emit_frame([&](auto tc) {
-#pragma unroll
-                        for (int i = 0; i < L1; ++i) emit(i, w[i], tc);
-                    });
+                    emit_frame([&](auto tc) { emit_column(0, w, tc); });
                 } else {
                     // exchange through LDS; column swizzle r ^ (k1 / U) keeps both the
                     // writes (fixed k1) and the reads (fixed r2) free of bank conflicts
@@ -621,20 +627,15 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
                         float2 w[U * L2];
                         split_exchange(eg, v, w, [&](int k) { return k * L2 + (r ^ (k / U)); },
                                        [&](int m) { return (r * U + m / L2) * L2 + (m % L2 ^ r); });
-                        make_gains();
 #pragma unroll
                         for (int u = 0; u < U; ++u) {
                             dft_regs<L2>(w + u * L2);
-                            emit_frame([&](auto tc) {
-#pragma unroll
-                                for (int k2 = 0; k2 < L2; ++k2) emit(u * L2 + k2, w[u * L2 + k2], tc);
-                            });
+                            emit_frame([&](auto tc) { emit_column(u * L2, w + u * L2, tc); });
                         }
                     } else {
                         float2 *e = reinterpret_cast<float2 *>(eg);
 #pragma unroll
                         for (int k1 = 0; k1 < L1; ++k1) e[k1 * L2 + (r ^ (k1 / U))] = v[k1];
-                        make_gains();
                         wave_sync();
 #pragma unroll
                         for (int u = 0; u < U; ++u) {
@@ -643,10 +644,7 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
 #pragma unroll
                             for (int r2 = 0; r2 < L2; ++r2) w[r2] = e[k1 * L2 + (r2 ^ r)];
                             dft_regs<L2>(w);
-                            emit_frame([&](auto tc) {
-#pragma unroll
-                                for (int k2 = 0; k2 < L2; ++k2) emit(u * L2 + k2, w[k2], tc);
-                            });
+                            emit_frame([&](auto tc) { emit_column(u * L2, w, tc); });
                         }
                     }
                 }

@@ -155,3 +155,32 @@ def test_delay_refused_for_batch_instances():
         with pytest.raises(mwax.MwaxError) as e:
             b.plans[0].set_delays(torch.zeros((4, 1), dtype=torch.float32, device="cuda"), 320, 0.0)
         assert e.value.status == mwax.MWAX_E_UNSUPPORTED
+
+
+@pytest.mark.parametrize("scale", [0.5, 30.0])
+@pytest.mark.parametrize("L", [32, 64, 128, 256, 512, 1024])
+def test_delay_fp16_gains(L, scale):
+    # a frame's first sample alone: every bin is exactly 127, so a binary16 value is
+    # 127 times the gain, rounded.  With the gain rounded to FP32 (a quarter of an ulp
+    # on average, at most two of the product's) and one FP32 product (a quarter) the
+    # value before the last rounding is off by up to 3/4 of 2^-24 of itself on average,
+    # and as many of the 2^-11 between two binary16 values fall to the other side
+    n_tiles, M = 4, 262144 // L
+    n = 2 * n_tiles
+    v = np.zeros((n, M, L, 2), np.int8)
+    v[:, :, 0, 0] = 127
+    dl = delay_table(n, M, seed=730 + L, scale=scale)
+    with Plan(make_config(n_tiles, L=L, T=M, xprec="fp16", max_samples=L * M)) as p:
+        p.set_delays(torch.from_numpy(dl).cuda(), L, synth.NU_C)
+        p.channelise(torch.from_numpy(v.reshape(n, M * L, 2)).cuda())
+        got = p.read_channelised().cpu().numpy()
+    d = dl.T.astype(np.float64)[:, None, :]                          # [M][1][n]
+    turns = (np.arange(L) - L // 2)[None, :, None] * d / L + (d * NU - np.rint(d * NU))
+    e = (int(math.log2(L)) + 1) // 2
+    want = 127.0 * 2.0 ** -e * np.stack([np.cos(2 * np.pi * turns), -np.sin(2 * np.pi * turns)], -1)
+    off = np.abs(got.astype(np.float64) - want.astype(np.float16).astype(np.float64))
+    ulp = np.spacing(np.abs(want).astype(np.float16)).astype(np.float64)
+    wrong, most = np.count_nonzero(off), 0.75 * 2.0 ** -13 * off.size
+    log(f"delay fp16 L={L} delays to {scale}: {wrong} of {off.size} values on the other side (bound {most:.0f})")
+    assert np.all(off <= ulp)
+    assert wrong < most + 4 * math.sqrt(most)
