@@ -232,3 +232,12 @@ def test_vis_weights_at_block_edges(n_in):
     want = oracle.vis_weights(f, 65)
     g = mwax.vis_weights(torch.from_numpy(f).cuda(), 65).cpu().numpy().astype(np.float64)
     assert g.shape == want.shape and np.all(np.abs(g - want) <= HALF_ULP * want)
+
+
+@pytest.mark.parametrize("n_in,subs,n_ints", [(33, 1, 2100), (64, 3, 2049), (130, 33, 420)])
+def test_vis_weights_many_blocks(n_in, subs, n_ints):
+    # more than 6,144 blocks of 32 inputs: blocks of 64, ragged and whole
+    f = flags_for(n_in, subs, n_ints, 0.2, seed=n_in)
+    want = oracle.vis_weights(f, subs)
+    g = mwax.vis_weights(torch.from_numpy(f).cuda(), subs).cpu().numpy().astype(np.float64)
+    assert g.shape == want.shape and np.all(np.abs(g - want) <= HALF_ULP * want)
