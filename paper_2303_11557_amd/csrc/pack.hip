@@ -141,36 +141,35 @@ __global__ __launch_bounds__(256) void pack_avg_kernel(PackArgs a) {
     reinterpret_cast<float2 *>(a.out)[(int64_t)o * a.P + p] = make_float2((float)(re / div), (float)(im / div));
 }
 
-// Tile-baseline order: a workgroup moves kBlB baselines of one tile row (tile a,
-// consecutive tiles b) x kBlC channels through LDS.  The products of a baseline row
-// are two rows of the triangle (the inputs of tile a), contiguous over the inputs
-// of the tiles b, so reads run along the inputs and writes along the channels.
+// Tile-baseline order: a workgroup moves kBlB consecutive baselines x kBlC channels
+// through LDS.  The products of the baselines of a tile row are two rows of the
+// triangle (the inputs of its tile), contiguous over the inputs of their second tiles,
+// so reads run along the inputs and writes along the channels.  Integer sources, which
+// read the auto of a row beside every value, have the loads of all of a thread's
+// channels in flight; the others are as fast without.
 constexpr int kBlB = 16, kBlC = 16;
 template <int S>
 __global__ __launch_bounds__(256) void pack_tilebl_kernel(PackArgs a) {
     __shared__ float2 img[kBlB][kBlC][5];    // [baseline][channel][product], padded
-    // workgroup -> (tile row ta, run of kBlB tiles tb): rows hold 1, .., ceil(nt / kBlB) runs
-    int run = blockIdx.x, ta = 0;
-    {
-        // rows kBlB k .. kBlB k + kBlB - 1 hold k + 1 runs each
-        int k = 0;
-        while (run >= kBlB * (k + 1)) {
-            run -= kBlB * (k + 1);
-            ++k;
-        }
-        ta = kBlB * k + run / (k + 1);
-        run %= k + 1;
-    }
-    const int nt = a.n_in / 2;
-    if (ta >= nt) return;
-    const int tb0 = run * kBlB, nb = min(kBlB, ta + 1 - tb0);
+    const int nt = a.n_in / 2, nbl = nt * (nt + 1) / 2;
+    const int bl0 = blockIdx.x * kBlB, nb = min(kBlB, nbl - bl0);
     const int c0 = blockIdx.y * kBlC, nc = min(kBlC, a.L - c0);
-    // lanes along the 2 kBlB inputs of the tiles b; 8 (channel, input of tile a) at a time
+    // lanes along the 2 kBlB inputs of the baselines' second tiles; 8 (channel, input of
+    // the first tile) at a time
     const int s = threadIdx.x % (2 * kBlB), k0 = threadIdx.x / (2 * kBlB);
-    for (int k = k0; k < 2 * nc; k += 256 / (2 * kBlB)) {
-        const int c = c0 + (k >> 1), p1 = k & 1;
-        const int r = 2 * ta + p1, n2 = 2 * tb0 + s;
-        if (s < 2 * nb) {
+    // tile row of the first baseline (uniform; FP32 holds every index exactly), then of the lane's
+    int ta = (int)((sqrtf(8.0f * (float)bl0 + 1.0f) - 1.0f) * 0.5f);
+    while (ta * (ta + 1) / 2 > bl0) --ta;
+    const int bl = bl0 + (s >> 1);
+    while ((ta + 1) * (ta + 2) / 2 <= bl) ++ta;
+    if (s < 2 * nb) {
+        const int n2 = 2 * (bl - ta * (ta + 1) / 2) + (s & 1);
+        // channels past the last are read as it
+        constexpr int kUnroll = is_int(S) ? 2 * kBlC / (256 / (2 * kBlB)) : 1;
+#pragma unroll kUnroll
+        for (int k = k0; k < 2 * kBlC; k += 256 / (2 * kBlB)) {
+            const int c = min(c0 + (k >> 1), a.L - 1), p1 = k & 1;
+            const int r = 2 * ta + p1;
             double2 v;
             if (n2 <= r) {
                 v = scaled<S>(a, c, (int64_t)r * (r + 1) / 2 + n2, auto_of(r));
@@ -182,10 +181,9 @@ __global__ __launch_bounds__(256) void pack_tilebl_kernel(PackArgs a) {
         }
     }
     __syncthreads();
-    const int64_t bl0 = (int64_t)ta * (ta + 1) / 2 + tb0;
     for (int u = threadIdx.x; u < nb * nc * 4; u += 256) {
         const int b = u / (nc * 4), rest = u - b * nc * 4;
-        reinterpret_cast<float2 *>(a.out)[((bl0 + b) * a.L + c0) * 4 + rest] = img[b][rest >> 2][rest & 3];
+        reinterpret_cast<float2 *>(a.out)[((int64_t)(bl0 + b) * a.L + c0) * 4 + rest] = img[b][rest >> 2][rest & 3];
     }
 }
 
@@ -225,8 +223,8 @@ static hipError_t launch_pack_source(const PackArgs &a, hipStream_t s) {
         if (a.F < 1 || a.L % a.F != 0) return hipErrorInvalidValue;
         hipLaunchKernelGGL(pack_avg_kernel<S>, dim3(gx, (unsigned)(a.L / a.F)), dim3(256), 0, s, a);
     } else if (a.order == MWAX_ORDER_TILE_BL) {
-        const int k = (a.n_in / 2 + kBlB - 1) / kBlB;   // tile rows in units of kBlB
-        hipLaunchKernelGGL(pack_tilebl_kernel<S>, dim3((unsigned)(kBlB * k * (k + 1) / 2), (unsigned)((a.L + kBlC - 1) / kBlC)),
+        const int nt = a.n_in / 2, nbl = nt * (nt + 1) / 2;
+        hipLaunchKernelGGL(pack_tilebl_kernel<S>, dim3((unsigned)((nbl + kBlB - 1) / kBlB), (unsigned)((a.L + kBlC - 1) / kBlC)),
                            dim3(256), 0, s, a);
     } else {
         // small outputs: fewer channels per thread, at least eight workgroups per CU
