@@ -358,3 +358,33 @@ def test_x_engine_averaging_keeps_small_imaginary_parts():
     want = oracle.fscrunch(127.0 * (s[..., :1] - 1j * s[..., 1:]), F)[..., 0]
     rest = np.arange(Lc // F) != Lc // F // 2
     assert np.array_equal(got[:, rest], want[:, rest].astype(np.complex64))
+
+
+@pytest.mark.parametrize("prec", ["int8", "fp16"])
+def test_x_engine_averaging_over_more_channels_than_its_table(prec):
+    # 320 fine channels per output channel in the 64-edge kernel (20 output channels x
+    # 8 workgroups x 2 segments: more than one per CU), whose table of channel weights
+    # holds 256 and is reloaded; against FP64 sums of the plan's own voltages
+    n_tiles, F, T = 100, 320, 12
+    n = 2 * n_tiles
+    v = torch.from_numpy(synth.gaussian_volts(n, 2 * T * L, seed=761, sources=[synth.Source(4.0, 900)], L=L)).cuda()
+    s = (5.0 * np.sqrt(L * 64.0) / 127.0 * (1.0 + 0.3 * np.arange(L) / L)).astype(np.float32)
+    rng = np.random.default_rng(5)
+    n1 = np.concatenate([[0, n - 1, n - 1], rng.integers(0, n, 42)])
+    n2 = np.concatenate([[0, n - 1, 0], rng.integers(0, n, 42)])
+    n1, n2 = np.maximum(n1, n2), np.minimum(n1, n2)
+    with Plan(make_config(n_tiles, L=L, T=T, xprec=prec, max_samples=2 * T * L)) as p:
+        if prec == "int8":
+            p.set_scales(s)
+        p.set_averaging(F)
+        p.channelise(v)
+        x = p.read_channelised().to(torch.float64)
+        p.correlate()
+        got = p.integrate(2)[:, :, torch.from_numpy(n1 * (n1 + 1) // 2 + n2).cuda()].cpu().numpy()
+    x = torch.view_as_complex(x)
+    ref = (x[:, :, torch.from_numpy(n1).cuda()] * x[:, :, torch.from_numpy(n2).cuda()].conj()).reshape(2, T, L, -1)
+    ref = ref.sum(1).cpu().numpy()
+    ref *= (s.astype(np.float64) ** 2)[:, None] if prec == "int8" else 2.0 ** (2 * ((13 + 1) // 2))
+    want = oracle.fscrunch(ref, F)
+    assert got.shape == want.shape == (2, L // F, n1.size)
+    assert rel_frob(got, want).max() < (F + 1) * 2.0 ** -24      # FP32 sums of F + 1 weighted terms
