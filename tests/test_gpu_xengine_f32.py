@@ -53,3 +53,19 @@ def test_matrix_core_fp32(n_tiles, L, T, split):
     ref = oracle.correlate(x[..., 0].astype(np.float64) + 1j * x[..., 1], T)
     err = np.linalg.norm(got - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
     assert got.shape == ref.shape and err.max() < 2e-6, err.max()
+
+
+@pytest.mark.parametrize("n_tiles", [116, 130])
+def test_matrix_core_fp32_many_tiles(n_tiles):
+    # 8 and 9 blocks of 32 along an edge, more than four workgroups per CU: four diagonal
+    # tiles dealt to three workgroups; an odd last row of blocks
+    n, L, T = 2 * n_tiles, 128, 33
+    rng = np.random.default_rng(n)
+    x = (rng.normal(size=(T, L, n, 2)) * 100.0).astype(np.float32)
+    with Plan(make_config(n_tiles, L=L, T=T, xprec="fp32", max_samples=L * T)) as p:
+        p.load_channelised(torch.from_numpy(x).cuda())
+        p.correlate()
+        got = p.integrate(1).cpu().numpy().astype(np.complex128)
+    ref = oracle.correlate(x[..., 0].astype(np.float64) + 1j * x[..., 1], T)
+    err = np.linalg.norm(got - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
+    assert got.shape == ref.shape and err.max() < 2e-6, err.max()
