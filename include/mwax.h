@@ -335,7 +335,7 @@ mwax_status mwax_kernel_time(mwax_plan p, int32_t family, double *total_ms, int6
  * length and integration time) on one GPU as one unit of device work per call:
  * the table-driven F-engine launches (one per distinct FFT length), the scale
  * calibration and a single persistent matrix-core X-engine launch that takes
- * 128 x 128 tiles of every instance from per-XCD work queues.  The sequence is
+ * tiles of every instance from per-XCD work queues.  The sequence is
  * captured once in a HIP graph and replayed on every call; only its device
  * work tables change (uploaded from pinned host memory ahead of the replay).
  *
@@ -377,8 +377,8 @@ mwax_status mwax_batch_run(mwax_batch b, const int8_t *const *d_volts, const int
 /* Autotuner: on the given block (as for mwax_batch_run, every n_samples[i] >
  * 0), channelise once, then time the persistent X-engine on the device for
  * candidate work shapes: per instance shape (inputs, L), the MFMA tile edge
- * (128 x 128 tiles, four waves of 64 x 64; or 64 x 64 tiles, four waves of
- * 32 x 32, which waste less of the diagonal tiles on small instances) and the
+ * (128: work items of four 64 x 64 blocks of the triangle, one per wave; or 64:
+ * four 32 x 32 blocks, which waste less of the diagonal on small instances) and the
  * number of row groups per work item (whole segments, or chunks of 4096 .. 128
  * row groups; INT8 only, chunks of one tile then flush with exact int64 atomic
  * adds), and the persistent grid size.  Each candidate is timed `trials` times

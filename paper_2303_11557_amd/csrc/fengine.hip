@@ -7,9 +7,8 @@
 //
 // One workgroup owns R inputs x G consecutive frames of one integration
 // segment = one 32-byte row group per (channel, input).  The raw int8 frames
-// are staged in LDS with coalesced 16-byte loads (INT8 at L = 1024: loaded by
-// the FFT lanes themselves, see FCfg::DIRECT); each FFT is computed by a
-// group of L2 lanes holding L1 = L / L2 points each:
+// are staged in LDS with coalesced 16-byte loads (L = 1024: loaded by the FFT
+// lanes themselves, see FCfg::DIRECT); each FFT is computed by a group of L2 lanes holding L1 = L / L2 points each:
 //   X[k1 + L1 k2] = sum_r W_L2^(r k2) W_L^(r k1) sum_n1 x[r + L2 n1] W_L1^(n1 k1)
 // (a two-pass Cooley-Tukey split): pass 1 in registers per lane, twiddle,
 // exchange of the L1 x L2 block through LDS, pass 2 in registers.  The
@@ -87,7 +86,7 @@ __device__ __forceinline__ double2 turn_by(double2 a, double2 b) {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
-constexpr int kThreads = 256;   // default workgroup size (see FCfg::THREADS)
+constexpr int kThreads = 256;   // workgroup size
 
 // Output-image padding per channel (bytes beyond R * 32), chosen so the packed
 // output writes of a wave fall in distinct LDS banks.
@@ -97,12 +96,13 @@ constexpr int cp_pad(int L, int XP) {
                        : (L <= 256 ? (XP == MWAX_X_INT8 ? 4 : 8) : 4)));
 }
 
+constexpr int64_t kLeast = 2048;   // workgroups that fill the device (about all that can be resident)
+
 // Work decomposition of one workgroup (THREADS threads) for length L and
 // output precision XP.  An FFT group is L2 lanes; a wave holds GPW groups.
 // Each group transforms FPG consecutive frames of one input, so that the
 // results of FPG frames leave in one packed LDS write; the workgroup covers
 // R inputs x G frames (one 32-byte row group per channel and input).
-constexpr int64_t kLeast = 2048;   // workgroups that fill the device (about all that can be resident)
 template <int L, int XP>
 struct FCfg {
     using SH = FftShape<L, XP>;
@@ -110,21 +110,19 @@ struct FCfg {
     static constexpr int G = PrecTraits<XP>::G, ES = PrecTraits<XP>::ES;
     // INT8 at 16 <= L <= 256: one frame per group (byte writes) holds fewer
     // registers than packing two frames' codes, for more waves per SIMD.  At
-    // L >= 512 (32 or 64 lanes per FFT) an INT8 group transforms two frames,
-    // so that a workgroup still covers the 16 frames of a row group, and
-    // L = 1024 (one FFT per wave) takes eight waves at every precision (two
-    // inputs per item for FP32: 64-byte runs per channel).  Binary16 keeps one
-    // frame per group (two would need 86 KB of LDS at L = 128, one workgroup per CU).
+    // L >= 512 (32 or 64 lanes per FFT) an INT8 group transforms two frames, so
+    // that its codes leave two at a time.  Binary16 keeps one frame per group (two
+    // would need 86 KB of LDS at L = 128, one workgroup per CU).
     static constexpr int FPG = XP == MWAX_X_INT8 ? (L >= 16 && L <= 256 ? 1 : 2) : 1;
-    // L = 1024: four waves whose lanes load their own samples straight from HBM (a
-    // lane's samples r + 64 n1 of a frame are one 128-byte line per load
+    // L = 1024 (one FFT per wave): the lanes load their own samples straight from HBM
+    // (a lane's samples r + 64 n1 of a frame are one 128-byte line per load
     // instruction), INT8 two packs of an item per wave in turn, binary16 two frames.
     // Without the staging area two (INT8) or three workgroups fit a CU, and one's
     // barriers and image store overlap the others' FFTs: INT8 2.34 instead of 1.86
     // TB/s, binary16 and FP32 see SPLIT.  (At L = 512, two 32-lane groups per wave,
     // INT8 ran at 2.04 instead of 2.37 TB/s this way.)
     static constexpr bool DIRECT = L == 1024;
-    static constexpr int THREADS = DIRECT ? kThreads : (L == 1024 ? 512 : kThreads);
+    static constexpr int THREADS = kThreads;
     static constexpr int P = SH::P;
     static constexpr int GPW = 64 / L2;
     static constexpr int NGWG = THREADS / 64 * GPW;   // FFT groups per workgroup
@@ -712,6 +710,9 @@ __global__ __launch_bounds__((FCfg<L, XP>::THREADS), (STATS || (DELAY && (XP != 
 
 // Batched form: workgroups [block0[d], block0[d+1]) of the launch work on
 // descriptor d (a segment of one plan of the batch); the rest return at once.
+// Not held to MINW waves: binary16 compiles to three per SIMD up to L = 512 as it is,
+// and at L = 1024 (two) a third changes nothing (60 and 96 tiles, 195 spectra: 165.5
+// us, held to three 164.9).
 template <int L, int XP, bool STATS>
 __global__ __launch_bounds__((FCfg<L, XP>::THREADS)) void fengine_batch_kernel(FBatchArgs b) {
     extern __shared__ __align__(16) uint8_t smem[];

@@ -280,9 +280,10 @@ constexpr int kXTileTiny = 32, kXSmallInputs = 64;
 // Workgroups per channel at a tile edge.
 int xengine_tile_count(int n_in, int te);
 
-// Persistent batched X-engine.  A work item is one 128 x 128 tile of one channel
-// of one segment over a chunk of its row groups, packed in 32 bits:
-//   desc (8 bits) | channel (10) | tile (8) | chunk (6)
+// Persistent batched X-engine.  A work item is a workgroup's share of the triangle of
+// one channel of one segment (four blocks of half a tile edge, see TriBlock in
+// xengine.hip) over a chunk of its row groups, packed in 32 bits:
+//   desc (8 bits) | channel (10) | share ("tile", 8) | chunk (6)
 // Items sit in 8 queues, one per XCD (workgroup b runs on XCD b mod 8); a
 // workgroup drains its own queue, then takes work from the others.  Chunks of
 // one (channel, tile) run concurrently only in segments with ksplit > 1, whose
