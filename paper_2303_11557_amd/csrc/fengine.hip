@@ -377,14 +377,14 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
             // gains turn by the same angle from one to the next: in FP64, whose roundings
             // do not reach FP32, two sincos per column and four multiply-adds per bin
             // instead of a sincos per bin (that of a bin in FP32 is off by 6e-8 rms, for
-            // delays of many samples by more; these by the one rounding to FP32).  Formed
+            // delays of many samples by more; these by the one rounding to FP32).  Taken
             // before the frame is loaded, when registers are free.  186 inputs, 1 s at L =
             // 256 / 1024: 461, 697 us; with a sincos per bin and two workgroups per CU
             // 752, 1,227.  INT8 and FP32 plans evaluate every bin.
             constexpr bool CHAIN = DELAY && XP == MWAX_X_FP16 && L2 > 1;
             constexpr int NT = P > 1 || L2 == 1 ? L1 : L2, NC = L1 / NT;   // bins of a column, columns
             double2 first[CHAIN ? NC : 1], by;
-            if constexpr (DELAY) {
+            auto take_delay = [&] {
                 float d = 0.0f;
                 if (nl < nrows && f < fvalid)
                     d = a.dl[(int64_t)(n0 + nl) * a.dl_ld + (a.dl_f0 + lf0 + f) / a.dl_fps];
@@ -399,7 +399,8 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
                         first[u] = turn((bin_of<L, XP>(r, u * NT) - L / 2) * ((double)d / L) + (ph - rint(ph)));
                     by = turn((double)d / NT);
                 }
-            }
+            };
+            if constexpr (CHAIN) take_delay();
 
             float2 v[L1];
             if constexpr (C::DIRECT) {
@@ -451,6 +452,7 @@ __device__ __forceinline__ void fengine_body(const FArgs &a, const int wg, const
                 }
             }
             dft_regs<L1>(v);
+            if constexpr (DELAY && !CHAIN) take_delay();
 
             // consume output slot i (FFT bin of this lane) with value X and, if CHAIN, gain
             // g; tc: the frame's place in its pack as a compile-time constant (see emit_frame)
