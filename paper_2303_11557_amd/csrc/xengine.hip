@@ -1280,33 +1280,30 @@ int device_cus() {
     return cus;
 }
 
-// Resident workgroups of the single-plan MFMA kernel on the current device.
-int resident_slots() {
-    static int slots = 0;
-    if (slots == 0) {
-        int per_cu = 0;
-        const int cus = device_cus();
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                &per_cu, reinterpret_cast<const void *>(&xengine_mfma<MWAX_X_INT8>), kThreads, 0) != hipSuccess ||
-            per_cu < 1)
-            per_cu = 1;
-        slots = cus * per_cu;
-    }
-    return slots;
-}
-
-// Chunks per tile: the fewest that minimise the number of workgroup waves per
-// unit of work, with at least kMinChunkGroups row groups per chunk.
+// Chunks per tile of an INT8 launch of items workgroups over ngrp row groups and pairs
+// integrators: those of the least cost, with at least kMinChunkGroups row groups to a
+// chunk.  Cost in row groups of a workgroup, as long as they take with two workgroups
+// on a CU (0.21 us for each): the K loops of the CU that gets the most chunks, one alone
+// on its CU running at 4/5 of the rate; and the flushes, of which a split launch has one
+// of atomic additions per chunk (less what runs beside other workgroups' K loops) and a
+// slot to clear.  Chunks even out the last round of workgroups, but only few or long
+// segments are worth it.  us from load to correlated, 1 / 2 / 4 / 8 chunks: 512 inputs,
+// 128 channels, 4,000 spectra 299 / 546 / 868 / 1,613, 40,000 2,465 / 2,376 / 2,451 /
+// 2,656; 256 channels, 2,500 382 / 933 / 1,666 / 3,180; 256 inputs, 128 channels, 10,000
+// 228 / 312 / 361 / 501, 40,000 851 / 786 / 789 / 885; 128 inputs, 40,000 558 / 358 /
+// 320 / 378; 80 inputs, 64 channels, 20,000 241 / 153 / 99 / 82.
 constexpr int kMinChunkGroups = 64;
-int pick_chunks(int64_t items, int ngrp, int slots) {
+int pick_chunks(int64_t items, int64_t pairs, int ngrp) {
+    const int cus = device_cus();
     int best = 1;
     double best_cost = 1e300;
     for (int k = 1; k <= 8; ++k) {
         if (k > 1 && (ngrp + k - 1) / k < kMinChunkGroups) break;
-        const double waves = (double)((items * k + slots - 1) / slots);
-        const double cost = waves / k;
-        if (cost < best_cost - 1e-9) {
-            best_cost = cost;
+        const double most = (double)((items * k + cus - 1) / cus), share = (double)pairs / cus;
+        const double loops = (most > 1.0 ? most : 1.25) * ngrp / k;
+        const double flushes = k == 1 ? 0.0022 * share : 0.0097 * share * k + 60.0;
+        if (loops + flushes < best_cost - 1e-9) {
+            best_cost = loops + flushes;
             best = k;
         }
     }
@@ -1321,7 +1318,7 @@ void set_chunks(int xprec, XArgs &a) {
     const int m = (a.n_in + kTile / 2 - 1) / (kTile / 2);
     a.sets = tri_sets(m);
     a.ntiles = tri_groups(m, a.sets);
-    if (a.nks != 1) a.nks = xprec == MWAX_X_INT8 ? pick_chunks((int64_t)a.ntiles * a.L, a.ngrp, resident_slots()) : 1;
+    if (a.nks != 1) a.nks = xprec == MWAX_X_INT8 ? pick_chunks((int64_t)a.ntiles * a.L, a.P * a.L, a.ngrp) : 1;
     // Unsplit, the last round of workgroups is shorter with some waves idle if that
     // brings as many workgroups to every CU (each has the same number of blocks then).
     // FP16, 512 inputs, 128 channels, two calls of 10,000 spectra: 10 workgroups per

@@ -55,3 +55,23 @@ def test_division_into_blocks(prec, n_tiles, L, T):
     ref = oracle.correlate(x[..., 0] + 1j * x[..., 1], T)
     got = got * 2.0 ** (-2 * ((int(np.log2(L)) + 1) // 2))
     assert np.linalg.norm(got - ref) / np.linalg.norm(ref) < 2e-6
+
+
+@pytest.mark.parametrize("T", [5000, 70000])
+def test_chunks_add_into_reused_slots(T):
+    # long segments of few workgroups: two or more chunks to a tile, added atomically
+    # into slots that earlier integrations left uncleared (int32 and int64 sums)
+    n_tiles, L, ints = 35, 1, 4
+    n = 2 * n_tiles
+    x = np.random.default_rng(T).integers(-127, 128, size=(T, L, n, 2)).astype(np.int8)
+    x[-1, :, :, :] = 127
+    got = []
+    with Plan(make_config(n_tiles, L=L, T=T, xprec="int8", max_samples=L * T)) as p:
+        d = torch.from_numpy(x).cuda()
+        for j in range(ints):
+            p.load_channelised(d if j % 2 == 0 else -d)          # the same sums
+            p.correlate()
+            got.append(p.integrate_raw(1)[0].cpu().numpy()[0])
+    ref = oracle.correlate_i64(x, T)[0]
+    for g in got:
+        assert np.array_equal(g, ref)
