@@ -167,13 +167,17 @@ struct FCfg {
     // share output lines) drift apart.  Measured at 256 tiles, 8 s: 65,536 at every
     // length but 256, where 131,072 is 10 % faster (32,768 - 262,144 swept).
     static constexpr int64_t GRID_CAP = L == 256 ? 131072 : 65536;
-    // most rounds of a single-plan launch (main_grid): eight, but FP32 at L >= 512, whose
-    // items write 64 or 32 bytes of a channel's 128-byte lines, loses more by the drift
-    // than the set-up costs: at L = 512 two, at L = 1024 one once three do not hold the
+    // most rounds of a single-plan launch (main_grid): eight, but where the drift costs
+    // more than the set-up.  FP32 at L >= 512, whose items write 64 or 32 bytes of a
+    // channel's 128-byte lines: at L = 512 two, at L = 1024 one once three do not hold the
     // launch to kLeast.  us in eight rounds / these: L = 512, 128 inputs x 400 spectra
     // 90 / 82, 512 x 400 340 / 307; L = 1024, 128 x 520 317 / 269, 256 x 1,200 1,509 /
-    // 1,192 (64 x 320: 71 in three, 90 in one).
+    // 1,192 (64 x 320: 71 in three, 90 in one).  And L = 8, 16, an FFT to a lane, which
+    // has next to no set-up: two and one.  20 tiles x 0.5 s, L = 8 INT8 27.0 / 25.4,
+    // binary16 31.0 / 28.2, FP32 47.2 / 41.4; L = 16, 64 tiles x 1 s 140 / 134, 207 /
+    // 199, 342 / 325.
     static constexpr int64_t most_rounds(int64_t items) {
+        if (L == 8 || L == 16) return 16 / L;
         return XP != MWAX_X_FP32 || L < 512 ? 8 : (L == 512 ? 2 : (items <= 3 * kLeast ? 3 : 1));
     }
 };
