@@ -62,11 +62,11 @@ __device__ __forceinline__ v16f mma_bf16(const uint4 &a, const uint4 &b, v16f c)
 // the weights are split into their pieces on the way into LDS.  Row n of a row
 // group sits at n ^ s within its eight rows, s = the 8-input half and the group's
 // low bits, so that the lanes of a read fall in distinct banks.
-// 32 beams, 256 tiles, 128 channels, 10,000 INT8 spectra: 0.55 ms (305 TFLOP/s of
-// the FP32 product, 3.0 TB/s of the 1.66 GB it cannot do without) against 1.86 ms
+// 32 beams, 256 tiles, 128 channels, 10,000 INT8 spectra: 0.57 ms (295 TFLOP/s of
+// the FP32 product, 2.9 TB/s of the 1.66 GB it cannot do without) against 1.86 ms
 // on the FP32 instructions, and half their error (2.9e-7 of the rms against
 // 5.7e-7: a sum rounds once per 16 inputs and piece, not once per input and
-// component).  Binary16, 8 to 96 beams: 1.75 to 1.95 times as fast.
+// component).  Binary16, 8 to 96 beams: 1.5 to 2 times as fast.
 // These instructions take bf16 denormals as zeros, so a weight's pieces and their
 // products with the voltages' (2^-24 at the least) have to be normal: its last bit,
 // 2^-23 of it, at least 2^(24 - 126), the weight at least 2^-79 (kLeastWeight).  And

@@ -263,9 +263,9 @@ struct XAvgArgs {
 };
 hipError_t launch_xengine_avg(int xprec, const XAvgArgs &a, hipStream_t s);
 
-// INT8 and FP16, more than kXSmallInputs inputs.  INT8 launches split every tile's row groups into chunks when
-// that fills the device's resident workgroup slots more evenly (chunks flush with
-// exact int64 atomic adds); FP16 runs whole segments.
+// INT8 and FP16, more than kXSmallInputs inputs.  INT8 launches split every tile's row
+// groups into chunks, which flush with exact integer atomic adds, when that evens out
+// what the CUs get by more than the flushes cost; FP16 runs whole segments.
 hipError_t launch_xengine(int xprec, const XArgs &a, hipStream_t s);
 // True if launch_xengine adds every partial sum into the integrators (INT8 split
 // into chunks); false if the first flush of a segment that starts
