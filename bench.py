@@ -673,7 +673,10 @@ def main_beamform(args):
     b_tf = flops / (b_ms / 1e3) / 1e12
     i_bytes = n_in * S * b_out + (M // 10) * (L // 4) * 2 * 4
     i_gbs = i_bytes / (i_ms / 1e3) / 1e9
-    peak = PEAK["fp32_vector_tflops"]         # the FP32 matrix-core peak is the same 157.3 TFLOP/s
+    # FP32 plans: the FP32 matrix-core peak (the vector one); INT8 and binary16: an exact
+    # product is three and six bf16 instructions, whose dense peak is the fp16 one
+    peak = {"fp32": PEAK["fp32_vector_tflops"], "int8": round(PEAK["fp16_tflops"] / 3, 1),
+            "fp16": round(PEAK["fp16_tflops"] / 6, 1)}[args.xprec]
     line = {
         "metric": "tied-array beamformer: coherent beams TFLOP/s and incoherent GB/s, 256 tiles",
         "value": cmac / (b_ms / 1e3), "unit": "CMAC/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
